@@ -73,11 +73,68 @@ __device__ __forceinline__ int tile_of_block(int remap)
     return (b & 7) * per + (b >> 3);
 }
 
-// Butterfly over groups of G lanes (G a power of two <= 64).
-template <class R, typename T>
-__device__ __forceinline__ T group_reduce(T v, int G)
+// Lane permutations inside the vector ALU, on 32- or 64-bit values: lane i
+// receives the value of another lane of its 16 (data-parallel primitives).
+template <int CTRL, int BANKS>
+__device__ __forceinline__ uint32_t dpp32(uint32_t old, uint32_t v)
 {
-    for (int off = G >> 1; off > 0; off >>= 1) v = R::comb(v, __shfl_xor(v, off, 64));
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, 0xf, BANKS, false);
+}
+template <int OFF>
+__device__ __forceinline__ uint32_t lane_xor32(uint32_t v)
+{
+    static_assert(OFF == 1 || OFF == 2 || OFF == 4 || OFF == 8, "inside a row of 16 lanes");
+    if constexpr (OFF == 1) return dpp32<0xB1, 0xf>(v, v);          // quad_perm [1,0,3,2]
+    if constexpr (OFF == 2) return dpp32<0x4E, 0xf>(v, v);          // quad_perm [2,3,0,1]
+    if constexpr (OFF == 8) return dpp32<0x128, 0xf>(v, v);         // row_ror:8
+    // lanes 0-3 and 8-11 of a row take lane i + 4, the others lane i - 4
+    return dpp32<0x114, 0xa>(dpp32<0x104, 0x5>(v, v), v);           // row_shl:4, row_shr:4
+}
+template <int OFF, typename T>
+__device__ __forceinline__ T lane_xor(T v)
+{
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, lane_xor32<OFF>(__builtin_bit_cast(uint32_t, v)));
+    } else {
+        const uint64_t u = __builtin_bit_cast(uint64_t, v);
+        const uint64_t hi = lane_xor32<OFF>((uint32_t)(u >> 32));
+        return __builtin_bit_cast(T, (hi << 32) | lane_xor32<OFF>((uint32_t)u));
+    }
+}
+// comb(v of this lane, v of lane ^ 16 or ^ 32): the swap leaves one half's
+// values in a and the other half's in b, in all lanes (comb commutes).
+template <class R, int OFF, typename T>
+__device__ __forceinline__ T swap_comb(T v)
+{
+    auto swap = [](uint32_t u) {
+        if constexpr (OFF == 16) return __builtin_amdgcn_permlane16_swap(u, u, false, false);
+        else return __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    };
+    if constexpr (sizeof(T) == 4) {
+        const auto p = swap(__builtin_bit_cast(uint32_t, v));
+        return R::comb(__builtin_bit_cast(T, (uint32_t)p[0]), __builtin_bit_cast(T, (uint32_t)p[1]));
+    } else {
+        const uint64_t u = __builtin_bit_cast(uint64_t, v);
+        const auto l = swap((uint32_t)u);
+        const auto h = swap((uint32_t)(u >> 32));
+        return R::comb(__builtin_bit_cast(T, ((uint64_t)h[0] << 32) | l[0]),
+                       __builtin_bit_cast(T, ((uint64_t)h[1] << 32) | l[1]));
+    }
+}
+
+// Butterfly over groups of 2^wl lanes (wl <= 6 and the same in the whole
+// wave), widest step first: every lane ends with the same sum.  The steps
+// stay in the vector ALU; through LDS permutes (two per 64-bit shuffle, each
+// waited for) they were the longest chain of a tile of short segments.
+template <class R, typename T>
+__device__ __forceinline__ T group_reduce(T v, int wl)
+{
+    if (wl >= 6) v = swap_comb<R, 32>(v);
+    if (wl >= 5) v = swap_comb<R, 16>(v);
+    if (wl >= 4) v = R::comb(v, lane_xor<8>(v));
+    if (wl >= 3) v = R::comb(v, lane_xor<4>(v));
+    if (wl >= 2) v = R::comb(v, lane_xor<2>(v));
+    if (wl >= 1) v = R::comb(v, lane_xor<1>(v));
     return v;
 }
 
@@ -88,7 +145,7 @@ __device__ __forceinline__ void block_reduce(T (&v)[NQ], T (*s_red)[kBlock / 64]
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-        T x = group_reduce<R>(v[q], 64);
+        T x = group_reduce<R>(v[q], 6);
         if (lane == 0) s_red[q][wave] = x;
     }
     __syncthreads();
@@ -117,13 +174,16 @@ __device__ __forceinline__ void nt_store(T *p, T v)
 //   epilogue(seg, r[NR], pre, acc) per-segment update, adds to acc[NQ]
 //   partials                      double* [NQ * ntiles] or null
 // Memory-level parallelism: every thread first issues all of its index /
-// value loads (kPer per thread), the segment-pointer loads and the epilogue
-// prefetches, then all of its gathers, so one tile costs about two memory
-// round trips before the LDS phases.
-constexpr int kPer = kTileNnzMax / kBlock;     // nonzeros per thread per tile
+// value loads, the segment-pointer loads and the epilogue prefetches, then
+// all of its gathers, so one tile costs about two memory round trips before
+// the LDS phases.  PER is the tile size over the 256 threads (1, 2, 4 or 8):
+// a small tile issues no repeated loads and takes little LDS.  With PER = 8
+// for every tile size, shuffles through LDS in the segment sums and an LDS
+// buffer of their results, an iteration of a 10k-nonzero LP took 10.3 us
+// (now 8.2), of a 1M-nonzero LP 34.8 us (28.6; update and output included).
 constexpr int kPre = 2;                         // prefetched segments per thread
 
-template <class Op>
+template <class Op, int PER>
 __global__ __launch_bounds__(kBlock) void k_tile(Op op0, const Tile *__restrict__ tiles,
                                                  int ntiles, const int *__restrict__ blk2tile,
                                                  int seg_stride,
@@ -139,8 +199,7 @@ __global__ __launch_bounds__(kBlock) void k_tile(Op op0, const Tile *__restrict_
     using R = typename Op::R;
     constexpr int NR = Op::NR;
     constexpr int NQ = Op::NQ > 0 ? Op::NQ : 1;
-    __shared__ AT s_prod[NR][kTileNnzMax];
-    __shared__ AT s_seg[NR][kMaxSegs];
+    __shared__ AT s_prod[NR][PER * kBlock];
     __shared__ int s_ptr[kMaxSegs + 1];
     __shared__ double s_red[NQ][kBlock / 64];
     __shared__ AT s_redp[NR][kBlock / 64];
@@ -162,49 +221,53 @@ __global__ __launch_bounds__(kBlock) void k_tile(Op op0, const Tile *__restrict_
     // so that each group of loads issues back to back and is waited for
     // once; per-element branches would put a wait after every load.
     // 1a. issue the tile's matrix stream (coalesced, non-temporal)
-    int jj[kPer];
-    MT aa[kPer];
-    int pp[kPer];             // where each product goes in LDS (gather-sorted tiles)
+    int jj[PER];
+    MT aa[PER];
+    int pp[PER];              // where each product goes in LDS (gather-sorted tiles)
     if (cnt > 0) {
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
+        for (int q = 0; q < PER; ++q) {
             const int e = min((int)threadIdx.x + q * kBlock, cnt - 1);
             jj[q] = nt_load(idx + nnz0 + e);
             aa[q] = nt_load(val + nnz0 + e);
         }
         if (pos) {
 #pragma unroll
-            for (int q = 0; q < kPer; ++q)
+            for (int q = 0; q < PER; ++q)
                 pp[q] = nt_load(pos + nnz0 + min((int)threadIdx.x + q * kBlock, cnt - 1));
         } else {
 #pragma unroll
-            for (int q = 0; q < kPer; ++q) pp[q] = threadIdx.x + q * kBlock;
+            for (int q = 0; q < PER; ++q) pp[q] = threadIdx.x + q * kBlock;
         }
     }
-    // 1b. segment pointers to LDS and the epilogue's vector loads
+    // 1b. segment pointers to LDS and the epilogue's vector loads; the second
+    // set only where the tile has more than kBlock segments (a uniform branch)
     typename Op::Pre pre[kPre];
     if (whole) {
-        constexpr int kPtrIt = (kMaxSegs + kBlock) / kBlock;   // covers nseg + 1 <= kMaxSegs + 1
-        int sp[kPtrIt];
+        const int sp0 = seg_ptr[d.seg_begin + min((int)threadIdx.x, nseg)];
+        op.prefetch(d.seg_begin + min((int)threadIdx.x, nseg - 1), pre[0]);
+        if (nseg >= kBlock) {
+            constexpr int kPtrIt = (kMaxSegs + kBlock) / kBlock;   // covers nseg + 1 <= kMaxSegs + 1
+            int sp[kPtrIt];
 #pragma unroll
-        for (int i = 0; i < kPtrIt; ++i)
-            sp[i] = seg_ptr[d.seg_begin + min((int)threadIdx.x + i * kBlock, nseg)];
+            for (int i = 1; i < kPtrIt; ++i)
+                sp[i] = seg_ptr[d.seg_begin + min((int)threadIdx.x + i * kBlock, nseg)];
+            op.prefetch(d.seg_begin + min((int)threadIdx.x + kBlock, nseg - 1), pre[1]);
 #pragma unroll
-        for (int q = 0; q < kPre; ++q)
-            op.prefetch(d.seg_begin + min((int)threadIdx.x + q * kBlock, nseg - 1), pre[q]);
-#pragma unroll
-        for (int i = 0; i < kPtrIt; ++i) {
-            const int s = threadIdx.x + i * kBlock;
-            if (s <= nseg) s_ptr[s] = sp[i] - nnz0;
+            for (int i = 1; i < kPtrIt; ++i) {
+                const int s = threadIdx.x + i * kBlock;
+                if (s <= nseg) s_ptr[s] = sp[i] - nnz0;
+            }
         }
+        if ((int)threadIdx.x <= nseg) s_ptr[threadIdx.x] = sp0 - nnz0;
     }
     // 1c. gathers (all issued before the first product is stored), products to LDS
     if (cnt > 0) {
-        AT pv[kPer][NR];
+        AT pv[PER][NR];
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) op.value(aa[q], jj[q], pv[q]);
+        for (int q = 0; q < PER; ++q) op.value(aa[q], jj[q], pv[q]);
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
+        for (int q = 0; q < PER; ++q) {
             const int e = threadIdx.x + q * kBlock;
             if (e < cnt) {
 #pragma unroll
@@ -219,11 +282,13 @@ __global__ __launch_bounds__(kBlock) void k_tile(Op op0, const Tile *__restrict_
     for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
 
     if (whole) {
-        // 2. segment reductions by groups of G lanes
-        const int G = 1 << d.width_log2;
+        // 2. segment reductions by groups of G lanes; a segment's result
+        // replaces its first product (only its own group reads that range)
+        const int wl = d.width_log2;
+        const int G = 1 << wl;
         const int lane = threadIdx.x & (G - 1);
-        const int ngrp = kBlock >> d.width_log2;
-        for (int s = threadIdx.x >> d.width_log2; s < nseg; s += ngrp) {
+        const int ngrp = kBlock >> wl;
+        for (int s = threadIdx.x >> wl; s < nseg; s += ngrp) {
             const int b = s_ptr[s], e = s_ptr[s + 1];
             AT r[NR];
 #pragma unroll
@@ -233,31 +298,27 @@ __global__ __launch_bounds__(kBlock) void k_tile(Op op0, const Tile *__restrict_
                 for (int q = 0; q < NR; ++q) r[q] = R::comb(r[q], s_prod[q][p]);
             }
 #pragma unroll
-            for (int q = 0; q < NR; ++q) r[q] = group_reduce<R>(r[q], G);
-            if (lane == 0) {
+            for (int q = 0; q < NR; ++q) r[q] = group_reduce<R>(r[q], wl);
+            if (lane == 0 && e > b) {
 #pragma unroll
-                for (int q = 0; q < NR; ++q) s_seg[q][s] = r[q];
+                for (int q = 0; q < NR; ++q) s_prod[q][b] = r[q];
             }
         }
         __syncthreads();
         // 3. fused epilogue, one thread per segment (coalesced vector I/O)
-#pragma unroll
-        for (int q = 0; q < kPre; ++q) {
-            const int s = threadIdx.x + q * kBlock;
-            if (s < nseg) {
-                AT r[NR];
-#pragma unroll
-                for (int z = 0; z < NR; ++z) r[z] = s_seg[z][s];
-                op.epilogue(d.seg_begin + s, r, pre[q], acc);
-            }
-        }
-        for (int s = threadIdx.x + kPre * kBlock; s < nseg; s += kBlock) {
+        auto finish = [&](int s, const typename Op::Pre &p1) {
+            const int b = s_ptr[s], e = s_ptr[s + 1];
             AT r[NR];
 #pragma unroll
-            for (int z = 0; z < NR; ++z) r[z] = s_seg[z][s];
+            for (int z = 0; z < NR; ++z) r[z] = e > b ? s_prod[z][b] : R::template id<AT>();
+            op.epilogue(d.seg_begin + s, r, p1, acc);
+        };
+        if ((int)threadIdx.x < nseg) finish(threadIdx.x, pre[0]);
+        if ((int)threadIdx.x + kBlock < nseg) finish(threadIdx.x + kBlock, pre[1]);
+        for (int s = threadIdx.x + kPre * kBlock; s < nseg; s += kBlock) {
             typename Op::Pre p1;
             op.prefetch(d.seg_begin + s, p1);
-            op.epilogue(d.seg_begin + s, r, p1, acc);
+            finish(s, p1);
         }
         if (Op::NQ > 0) {
             block_reduce<SumOp, NQ>(acc, s_red);

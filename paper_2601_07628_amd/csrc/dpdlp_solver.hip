@@ -467,9 +467,17 @@ static void launch_tiles(dpdlp_problem *P, const Op &op, const TileSet &ts, cons
     if (ts.n == 0) return;
     const int remap = P->prm.xcd_remap ? 1 : 0;
     const int grid = ts.blk2tile ? ts.grid : (remap ? ((ts.n + 7) / 8) * 8 : ts.n);
-    hipLaunchKernelGGL(k_tile<Op>, dim3(grid), dim3(kBlock), 0, P->s, op, ts.d, ts.n, ts.blk2tile,
-                       ts.seg_stride, seg_ptr, idx, val, (const uint16_t *)ts.pos,
-                       (typename Op::AT *)P->carries, remap);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), 0, P->s, op, ts.d, ts.n, ts.blk2tile,
+                           ts.seg_stride, seg_ptr, idx, val, (const uint16_t *)ts.pos,
+                           (typename Op::AT *)P->carries, remap);
+    };
+    // nonzeros per thread: as many as the largest tile needs
+    const int per = (P->prm.tile_nnz + kBlock - 1) / kBlock;
+    if (per <= 1) go(k_tile<Op, 1>);
+    else if (per <= 2) go(k_tile<Op, 2>);
+    else if (per <= 4) go(k_tile<Op, 4>);
+    else go(k_tile<Op, 8>);
     if (ts.nsplit)
         hipLaunchKernelGGL(k_split_fix<Op>, dim3((ts.nsplit + 63) / 64), dim3(64), 0, P->s, op,
                            ts.splits, ts.nsplit, ts.n, (const typename Op::AT *)P->carries);

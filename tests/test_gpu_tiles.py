@@ -1,0 +1,40 @@
+"""The tile kernels at the edges of their instantiations: nonzeros per thread
+(1, 2, 4, 8 by tile size) and every width of the segment reduction (1 to 64
+lanes), against the CPU oracle.  Bar: the iterates' 1e-10 of the parity tests
+(FP64 sums of up to 80 terms in another order differ by some 1e-15)."""
+import numpy as np
+import pytest
+
+import lpgen
+from tests.test_gpu_parity import D, O, fixed_run  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def ragged_lp(mean, seed, m=2311, n=1777):
+    """Rows of 0 to 2 mean nonzeros, every seventh one empty, one free row."""
+    rng = np.random.default_rng(seed)
+    deg = rng.integers(0, 2 * mean + 1, size=m)
+    deg[::7] = 0
+    deg = np.minimum(deg, n)
+    rows = np.repeat(np.arange(m), deg)
+    cols = np.concatenate([np.sort(rng.choice(n, size=d, replace=False)) for d in deg])
+    rp = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    val = rng.standard_normal(rows.size)
+    x = rng.uniform(-1, 1, n)
+    ax = np.bincount(rows, weights=val * x[cols], minlength=m)
+    lo = np.where(rng.random(m) < 0.5, ax, ax - 0.5)
+    hi = np.where(rng.random(m) < 0.5, np.maximum(lo, ax), np.inf)
+    lo[3], hi[3] = -np.inf, np.inf
+    return lpgen.LP(m, n, rp, cols.astype(np.int32), val, rng.standard_normal(n), lo, hi,
+                    np.full(n, -1.0), np.full(n, 1.0), name=f"ragged{mean}")
+
+
+@pytest.mark.parametrize("tile_nnz", [96, 256, 257, 512, 513, 1024, 1025, 2048])
+def test_tile_sizes_around_the_instantiations(D, O, tile_nnz):  # noqa: F811
+    fixed_run(D, O, ragged_lp(6, tile_nnz), 130, gpu_kw=dict(tile_nnz=tile_nnz))
+
+
+@pytest.mark.parametrize("mean", [1, 2, 4, 8, 16, 40])
+def test_segment_reduction_widths(D, O, mean):  # noqa: F811
+    fixed_run(D, O, ragged_lp(mean, 50 + mean), 130)
