@@ -69,6 +69,11 @@ void sort_tiles_by_gather(const std::vector<Tile> &tiles, hvec<int32_t> &idx,
 // Slices are S contiguous ranges of the gathered index that hold about
 // nnz / S nonzeros each; gptr[nidx + 1] is the gathered dimension's own
 // pointer array (its nonzero counts as prefix sums).
+// Width of the FP64 segment sums: for every whole tile the 2^w lanes per
+// segment with the least modelled time of the tile's four waves goes into
+// bits 8.. of width_log2 (bits 0-7 keep the width from the mean length).
+void choose_sum_widths(std::vector<Tile> &tiles, const int32_t *ptr);
+
 void slice_bounds(const hvec<int32_t> &gptr, int32_t nidx, int32_t S,
                   std::vector<int32_t> &bounds);
 void slice_format(const hvec<int32_t> &ptr, const hvec<int32_t> &idx, const hvec<int32_t> &gptr,

@@ -47,10 +47,15 @@ __device__ __forceinline__ T clampv(T v, T lo, T hi)
     return v < lo ? lo : (v > hi ? hi : v);
 }
 
-template <typename T>
+// Loads and stores of what a pass touches once.  NT: past the caches
+// (non-temporal), for passes whose data would only push the gathered vectors
+// out; otherwise plain, so that what one pass reads stays in the Infinity
+// Cache for the next (the rule is at streams_fit_cache()).
+template <bool NT = true, typename T>
 __device__ __forceinline__ T nt_load(const T *p)
 {
-    return __builtin_nontemporal_load(p);
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
 }
 
 struct SumOp {
@@ -159,10 +164,11 @@ __device__ __forceinline__ void block_reduce(T (&v)[NQ], T (*s_red)[kBlock / 64]
     }
 }
 
-template <typename T>
+template <bool NT = true, typename T>
 __device__ __forceinline__ void nt_store(T *p, T v)
 {
-    __builtin_nontemporal_store(v, p);
+    if constexpr (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
 }
 
 // Generic tile kernel.  Op supplies:
@@ -183,7 +189,7 @@ __device__ __forceinline__ void nt_store(T *p, T v)
 // (now 8.2), of a 1M-nonzero LP 34.8 us (28.6; update and output included).
 constexpr int kPre = 2;                         // prefetched segments per thread
 
-template <class Op, int PER>
+template <class Op, int PER, bool NT>
 __global__ __launch_bounds__(kBlock) void k_tile(Op op0, const Tile *__restrict__ tiles,
                                                  int ntiles, const int *__restrict__ blk2tile,
                                                  int seg_stride,
@@ -228,13 +234,13 @@ __global__ __launch_bounds__(kBlock) void k_tile(Op op0, const Tile *__restrict_
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             const int e = min((int)threadIdx.x + q * kBlock, cnt - 1);
-            jj[q] = nt_load(idx + nnz0 + e);
-            aa[q] = nt_load(val + nnz0 + e);
+            jj[q] = nt_load<NT>(idx + nnz0 + e);
+            aa[q] = nt_load<NT>(val + nnz0 + e);
         }
         if (pos) {
 #pragma unroll
             for (int q = 0; q < PER; ++q)
-                pp[q] = nt_load(pos + nnz0 + min((int)threadIdx.x + q * kBlock, cnt - 1));
+                pp[q] = nt_load<NT>(pos + nnz0 + min((int)threadIdx.x + q * kBlock, cnt - 1));
         } else {
 #pragma unroll
             for (int q = 0; q < PER; ++q) pp[q] = threadIdx.x + q * kBlock;
@@ -245,14 +251,14 @@ __global__ __launch_bounds__(kBlock) void k_tile(Op op0, const Tile *__restrict_
     typename Op::Pre pre[kPre];
     if (whole) {
         const int sp0 = seg_ptr[d.seg_begin + min((int)threadIdx.x, nseg)];
-        op.prefetch(d.seg_begin + min((int)threadIdx.x, nseg - 1), pre[0]);
+        op.template prefetch<NT>(d.seg_begin + min((int)threadIdx.x, nseg - 1), pre[0]);
         if (nseg >= kBlock) {
             constexpr int kPtrIt = (kMaxSegs + kBlock) / kBlock;   // covers nseg + 1 <= kMaxSegs + 1
             int sp[kPtrIt];
 #pragma unroll
             for (int i = 1; i < kPtrIt; ++i)
                 sp[i] = seg_ptr[d.seg_begin + min((int)threadIdx.x + i * kBlock, nseg)];
-            op.prefetch(d.seg_begin + min((int)threadIdx.x + kBlock, nseg - 1), pre[1]);
+            op.template prefetch<NT>(d.seg_begin + min((int)threadIdx.x + kBlock, nseg - 1), pre[1]);
 #pragma unroll
             for (int i = 1; i < kPtrIt; ++i) {
                 const int s = threadIdx.x + i * kBlock;
@@ -284,7 +290,9 @@ __global__ __launch_bounds__(kBlock) void k_tile(Op op0, const Tile *__restrict_
     if (whole) {
         // 2. segment reductions by groups of G lanes; a segment's result
         // replaces its first product (only its own group reads that range)
-        const int wl = d.width_log2;
+        // (FP32 sums keep the width of their first layout: another order of
+        // additions would change results in their last bits)
+        const int wl = (sizeof(AT) == 8 ? d.width_log2 >> 8 : d.width_log2) & 0xff;
         const int G = 1 << wl;
         const int lane = threadIdx.x & (G - 1);
         const int ngrp = kBlock >> wl;
@@ -293,7 +301,19 @@ __global__ __launch_bounds__(kBlock) void k_tile(Op op0, const Tile *__restrict_
             AT r[NR];
 #pragma unroll
             for (int q = 0; q < NR; ++q) r[q] = R::template id<AT>();
-            for (int p = b + lane; p < e; p += G) {
+            int p = b + lane;
+            for (; p + 3 * G < e; p += 4 * G) {       // 4 reads in flight, added in order
+                AT w[4][NR];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int q = 0; q < NR; ++q) w[u][q] = s_prod[q][p + u * G];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int q = 0; q < NR; ++q) r[q] = R::comb(r[q], w[u][q]);
+            }
+            for (; p < e; p += G) {
 #pragma unroll
                 for (int q = 0; q < NR; ++q) r[q] = R::comb(r[q], s_prod[q][p]);
             }
@@ -311,13 +331,13 @@ __global__ __launch_bounds__(kBlock) void k_tile(Op op0, const Tile *__restrict_
             AT r[NR];
 #pragma unroll
             for (int z = 0; z < NR; ++z) r[z] = e > b ? s_prod[z][b] : R::template id<AT>();
-            op.epilogue(d.seg_begin + s, r, p1, acc);
+            op.template epilogue<NT>(d.seg_begin + s, r, p1, acc);
         };
         if ((int)threadIdx.x < nseg) finish(threadIdx.x, pre[0]);
         if ((int)threadIdx.x + kBlock < nseg) finish(threadIdx.x + kBlock, pre[1]);
         for (int s = threadIdx.x + kPre * kBlock; s < nseg; s += kBlock) {
             typename Op::Pre p1;
-            op.prefetch(d.seg_begin + s, p1);
+            op.template prefetch<NT>(d.seg_begin + s, p1);
             finish(s, p1);
         }
         if (Op::NQ > 0) {
@@ -380,8 +400,8 @@ __global__ __launch_bounds__(64) void k_split_fix(Op op0, const SplitSeg *__rest
 #pragma unroll
     for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
     typename Op::Pre p1;
-    op.prefetch(sg.seg, p1);
-    op.epilogue(sg.seg, r, p1, acc);
+    op.template prefetch<true>(sg.seg, p1);
+    op.template epilogue<true>(sg.seg, r, p1, acc);
     if (Op::NQ > 0)
         for (int pc = 0; pc < sg.npieces; ++pc)
             for (int q = 0; q < Op::NQ; ++q)
@@ -434,18 +454,18 @@ struct PrimalOp {
     int j = 0;
     struct Pre { T x, c, lo, hi, xa; };
     __device__ void value(MT v, int j, AT *out) const { out[0] = v * y[j]; }
-    __device__ void prefetch(int j, Pre &p) const
+    template <bool NT> __device__ void prefetch(int j, Pre &p) const
     {
-        p.x = nt_load(x + j); p.c = nt_load(c + j); p.lo = nt_load(lo + j);
-        p.hi = nt_load(hi + j); p.xa = nt_load(xa + j);
+        p.x = nt_load<NT>(x + j); p.c = nt_load<NT>(c + j); p.lo = nt_load<NT>(lo + j);
+        p.hi = nt_load<NT>(hi + j); p.xa = nt_load<NT>(xa + j);
     }
-    __device__ void epilogue(int j, const AT *r, const Pre &p, double *) const
+    template <bool NT> __device__ void epilogue(int j, const AT *r, const Pre &p, double *) const
     {
         const T g = p.c - r[0];
         const T xk = p.x;
         const T xhv = clampv(xk - tau * g, p.lo, p.hi);
         xbar[j] = T(2) * xhv - xk;
-        nt_store(x + j, a * ((T(1) + gamma) * xhv - gamma * xk) + b * p.xa);
+        nt_store<NT>(x + j, a * ((T(1) + gamma) * xhv - gamma * xk) + b * p.xa);
         if (write_hat) {
             xh[j] = (double)xhv;
             dx[j] = (double)xk - (double)xhv;
@@ -464,19 +484,19 @@ struct PrimalQPOp : PrimalOp<T> {
     using Base = PrimalOp<T>;
     const T *__restrict__ q;
     struct Pre { T x, c, lo, hi, xa, q; };
-    __device__ void prefetch(int j, Pre &p) const
+    template <bool NT> __device__ void prefetch(int j, Pre &p) const
     {
-        p.x = nt_load(this->x + j); p.c = nt_load(this->c + j); p.lo = nt_load(this->lo + j);
-        p.hi = nt_load(this->hi + j); p.xa = nt_load(this->xa + j); p.q = nt_load(q + j);
+        p.x = nt_load<NT>(this->x + j); p.c = nt_load<NT>(this->c + j); p.lo = nt_load<NT>(this->lo + j);
+        p.hi = nt_load<NT>(this->hi + j); p.xa = nt_load<NT>(this->xa + j); p.q = nt_load<NT>(q + j);
     }
-    __device__ void epilogue(int j, const T *r, const Pre &p, double *) const
+    template <bool NT> __device__ void epilogue(int j, const T *r, const Pre &p, double *) const
     {
         const T g = p.c - r[0];
         const T xk = p.x;
         const T tau = this->tau;
         const T xhv = clampv((xk - tau * g) / (T(1) + tau * p.q), p.lo, p.hi);
         this->xbar[j] = T(2) * xhv - xk;
-        nt_store(this->x + j, this->a * ((T(1) + this->gamma) * xhv - this->gamma * xk) + this->b * p.xa);
+        nt_store<NT>(this->x + j, this->a * ((T(1) + this->gamma) * xhv - this->gamma * xk) + this->b * p.xa);
         if (this->write_hat) {
             this->xh[j] = (double)xhv;
             this->dx[j] = (double)xk - (double)xhv;
@@ -514,11 +534,11 @@ struct DualOp {
     int j = 0;
     struct Pre { T y, lo, hi, ya; };
     __device__ void value(MT v, int j, AT *out) const { out[0] = v * xbar[j]; }
-    __device__ void prefetch(int i, Pre &p) const
+    template <bool NT> __device__ void prefetch(int i, Pre &p) const
     {
-        p.y = y[i]; p.lo = nt_load(lo + i); p.hi = nt_load(hi + i); p.ya = nt_load(ya + i);
+        p.y = y[i]; p.lo = nt_load<NT>(lo + i); p.hi = nt_load<NT>(hi + i); p.ya = nt_load<NT>(ya + i);
     }
-    __device__ void epilogue(int i, const AT *r, const Pre &p, double *) const
+    template <bool NT> __device__ void epilogue(int i, const AT *r, const Pre &p, double *) const
     {
         const T yk = p.y;
         const T w = yk / sigma - r[0];
@@ -544,8 +564,8 @@ struct PartialOp {
     double *partials;
     using Pre = NoPre;
     __device__ void value(MT a, int j, AT *o) const { o[0] = a * v[j]; }
-    __device__ void prefetch(int, Pre &) const {}
-    __device__ void epilogue(int g, const AT *r, const Pre &, double *) const
+    template <bool NT> __device__ void prefetch(int, Pre &) const {}
+    template <bool NT> __device__ void epilogue(int g, const AT *r, const Pre &, double *) const
     {
         partial[g] = r[0];
     }
@@ -569,8 +589,8 @@ struct PartialOp2 {
         o[0] = a * v[j];
         o[1] = a * v2[j];
     }
-    __device__ void prefetch(int, Pre &) const {}
-    __device__ void epilogue(int g, const AT *r, const Pre &, double *) const
+    template <bool NT> __device__ void prefetch(int, Pre &) const {}
+    template <bool NT> __device__ void epilogue(int g, const AT *r, const Pre &, double *) const
     {
         partial[g] = r[0];
         partial[G + g] = r[1];
@@ -586,7 +606,7 @@ struct PartialOp2 {
 // Op::NR = 2 the second right-hand side's partials start G entries later.
 // Ops with NQ > 0 (check passes) leave per-block partial sums in
 // op.partials[q * gridDim.x + block].
-template <class Op>
+template <class Op, bool NT>
 __global__ __launch_bounds__(kBlock) void k_combine(Op op0, int nseg, int S,
                                                     const typename Op::AT *__restrict__ partial,
                                                     const uint8_t *__restrict__ mask,
@@ -604,7 +624,7 @@ __global__ __launch_bounds__(kBlock) void k_combine(Op op0, int nseg, int S,
     Op op = op0;
     op.resolve();
     typename Op::Pre p;
-    if (in) op.prefetch(j, p);
+    if (in) op.template prefetch<NT>(j, p);
     AT r[NR];
 #pragma unroll
     for (int z = 0; z < NR; ++z) r[z] = SumOp::template id<AT>();
@@ -643,7 +663,7 @@ __global__ __launch_bounds__(kBlock) void k_combine(Op op0, int nseg, int S,
     double acc[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
-    if (in) op.epilogue(j, r, p, acc);
+    if (in) op.template epilogue<NT>(j, r, p, acc);
     if (Op::NQ > 0) {
         block_reduce<SumOp, NQ>(acc, s_red);
         if (threadIdx.x == 0)
@@ -682,8 +702,8 @@ struct CheckRowOp {
         out[1] = v * dx[j];
     }
     using Pre = NoPre;
-    __device__ void prefetch(int, Pre &) const {}
-    __device__ void epilogue(int i, const AT *r, const Pre &, double *acc) const
+    template <bool NT> __device__ void prefetch(int, Pre &) const {}
+    template <bool NT> __device__ void epilogue(int i, const AT *r, const Pre &, double *acc) const
     {
         const double axi = r[0] / dr[i];
         const double res = axi - clampv(axi, lo0[i], hi0[i]);
@@ -725,8 +745,8 @@ struct CheckColOp {
     double tau;
     __device__ void value(MT v, int i, AT *out) const { out[0] = v * yh[i]; }
     using Pre = NoPre;
-    __device__ void prefetch(int, Pre &) const {}
-    __device__ void epilogue(int j, const AT *r, const Pre &, double *acc) const
+    template <bool NT> __device__ void prefetch(int, Pre &) const {}
+    template <bool NT> __device__ void epilogue(int j, const AT *r, const Pre &, double *acc) const
     {
         // a QP (Sec. 6) adds Q x to the gradient, x^T Q x / 2 to the primal
         // objective and takes it off the dual one; q~ x~ = D_c (Q x) and
@@ -764,8 +784,8 @@ struct SpmvOp {
         o[0] = div ? v * (in[j] / *div) : v * in[j];
     }
     using Pre = NoPre;
-    __device__ void prefetch(int, Pre &) const {}
-    __device__ void epilogue(int s, const AT *r, const Pre &, double *acc) const
+    template <bool NT> __device__ void prefetch(int, Pre &) const {}
+    template <bool NT> __device__ void epilogue(int s, const AT *r, const Pre &, double *acc) const
     {
         out[s] = r[0];
         acc[0] += r[0] * r[0];
@@ -788,8 +808,8 @@ struct LanczosOp {
     double *partials;
     __device__ void value(MT v, int j, AT *o) const { o[0] = v * in[j]; }
     struct Pre { double o; };
-    __device__ void prefetch(int s, Pre &p) const { p.o = first ? 0.0 : out[s]; }
-    __device__ void epilogue(int s, const AT *r, const Pre &p, double *acc) const
+    template <bool NT> __device__ void prefetch(int s, Pre &p) const { p.o = first ? 0.0 : out[s]; }
+    template <bool NT> __device__ void epilogue(int s, const AT *r, const Pre &p, double *acc) const
     {
         const double a = *nin;
         double v = r[0] / a;
@@ -810,8 +830,8 @@ struct AbsMaxOp {
     double *partials;
     __device__ void value(MT v, int, AT *o) const { o[0] = fabs(v); }
     using Pre = NoPre;
-    __device__ void prefetch(int, Pre &) const {}
-    __device__ void epilogue(int s, const AT *r, const Pre &, double *) const
+    template <bool NT> __device__ void prefetch(int, Pre &) const {}
+    template <bool NT> __device__ void epilogue(int s, const AT *r, const Pre &, double *) const
     {
         f[s] = r[0] > 0.0 ? 1.0 / sqrt(r[0]) : 1.0;
     }
@@ -826,8 +846,8 @@ struct AbsPowSumOp {
     double p;
     __device__ void value(MT v, int, AT *o) const { o[0] = p == 1.0 ? fabs(v) : pow(fabs(v), p); }
     using Pre = NoPre;
-    __device__ void prefetch(int, Pre &) const {}
-    __device__ void epilogue(int s, const AT *r, const Pre &, double *) const
+    template <bool NT> __device__ void prefetch(int, Pre &) const {}
+    template <bool NT> __device__ void epilogue(int s, const AT *r, const Pre &, double *) const
     {
         f[s] = r[0] > 0.0 ? 1.0 / sqrt(r[0]) : 1.0;
     }

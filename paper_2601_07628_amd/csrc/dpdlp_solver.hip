@@ -69,9 +69,10 @@ __global__ __launch_bounds__(kBlock) void k_scale_vals(const Tile *__restrict__ 
     if (t >= ntiles) return;
     const Tile d = tiles[t];
     const int nseg = d.seg_end - d.seg_begin;
-    const int G = 1 << d.width_log2;
+    const int wl = d.width_log2 & 0xff;
+    const int G = 1 << wl;
     const int lane = threadIdx.x & (G - 1);
-    for (int s = threadIdx.x >> d.width_log2; s < nseg; s += kBlock >> d.width_log2) {
+    for (int s = threadIdx.x >> wl; s < nseg; s += kBlock >> wl) {
         const int seg = d.seg_begin + s;
         const int b = max(seg_ptr[seg], d.nnz_begin), e = min(seg_ptr[seg + 1], d.nnz_end);
         const double fs = fseg[seg];
@@ -460,6 +461,32 @@ static int dalloc(dpdlp_problem *P, T **p, size_t count)
 
 static inline unsigned nblk(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
+// Whether one iteration's data (both formats and the vectors, in the current
+// precision) stays in the 256 MB Infinity Cache from one pass to the next:
+// then the streams use plain loads, beyond it non-temporal ones.  Measured
+// (64 iterations, plain / non-temporal, ms): a 228 MB LASSO 5.93 / 6.76,
+// FP32-mixed 204 MB 7.70 / 8.46, a 230 MB skewed LP 7.73 / 7.81, a 252 MB
+// transportation LP 3.79 / 4.06; past the size, 295 MB 9.70 / 9.51,
+// 328 MB 11.23 / 11.03, 1.3 GB 42.5 / 38.9 (306 MB in FP32: 11.4 / 11.7).
+static bool streams_fit_cache(const dpdlp_problem *P)
+{
+    const double vb = P->in_fp32 ? 4.0 : 8.0;
+    const double bytes = 2.0 * (4.0 + vb) * (double)P->nnz + vb * (8.0 * P->n + 6.0 * P->m);
+    return bytes <= 256.0 * (1 << 20);
+}
+
+template <class Op>
+static void launch_combine(dpdlp_problem *P, const Op &op, int nseg, const SlicedSet &ss,
+                           const typename Op::AT *partial)
+{
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(nblk(nseg)), dim3(kBlock), 0, P->s, op, nseg, ss.S, partial,
+                           ss.mask, ss.cbase, ss.G);
+    };
+    if (streams_fit_cache(P)) go(k_combine<Op, false>);
+    else go(k_combine<Op, true>);
+}
+
 template <class Op>
 static void launch_tiles(dpdlp_problem *P, const Op &op, const TileSet &ts, const int *seg_ptr,
                          const int *idx, const typename Op::MT *val)
@@ -474,10 +501,15 @@ static void launch_tiles(dpdlp_problem *P, const Op &op, const TileSet &ts, cons
     };
     // nonzeros per thread: as many as the largest tile needs
     const int per = (P->prm.tile_nnz + kBlock - 1) / kBlock;
-    if (per <= 1) go(k_tile<Op, 1>);
-    else if (per <= 2) go(k_tile<Op, 2>);
-    else if (per <= 4) go(k_tile<Op, 4>);
-    else go(k_tile<Op, 8>);
+    auto pick = [&](auto nt) {
+        constexpr bool NT = decltype(nt)::value;
+        if (per <= 1) go(k_tile<Op, 1, NT>);
+        else if (per <= 2) go(k_tile<Op, 2, NT>);
+        else if (per <= 4) go(k_tile<Op, 4, NT>);
+        else go(k_tile<Op, 8, NT>);
+    };
+    if (streams_fit_cache(P)) pick(std::false_type{});
+    else pick(std::true_type{});
     if (ts.nsplit)
         hipLaunchKernelGGL(k_split_fix<Op>, dim3((ts.nsplit + 63) / 64), dim3(64), 0, P->s, op,
                            ts.splits, ts.nsplit, ts.n, (const typename Op::AT *)P->carries);
@@ -541,8 +573,7 @@ static void run_primal(dpdlp_problem *P, const Op &op, const T *y, const T *vt)
         po.v = y; po.partial = (T *)P->part_slices; po.partials = nullptr;
         launch_tiles(P, po, P->sc.ts, P->sc.ptr, P->sc.idx,
                      (const T *)(sizeof(T) == 8 ? (const void *)P->sc.val : (const void *)P->sc.val32));
-        hipLaunchKernelGGL(k_combine<Op>, dim3(nblk(P->n)), dim3(kBlock), 0, P->s, op, P->n,
-                           P->sc.S, (const T *)P->part_slices, P->sc.mask, P->sc.cbase, P->sc.G);
+        launch_combine(P, op, P->n, P->sc, (const T *)P->part_slices);
         return;
     }
     launch_tiles(P, op, P->tc, P->cp, P->ri, vt);
@@ -594,8 +625,7 @@ static void launch_dual(dpdlp_problem *P, const T *xbar, const T *lo, const T *h
         po.v = xbar; po.partial = (T *)P->part_slices; po.partials = nullptr;
         launch_tiles(P, po, P->sr.ts, P->sr.ptr, P->sr.idx,
                      (const T *)(sizeof(T) == 8 ? (const void *)P->sr.val : (const void *)P->sr.val32));
-        hipLaunchKernelGGL(k_combine<DualOp<T>>, dim3(nblk(P->m)), dim3(kBlock), 0, P->s, op, P->m,
-                           P->sr.S, (const T *)P->part_slices, P->sr.mask, P->sr.cbase, P->sr.G);
+        launch_combine(P, op, P->m, P->sr, (const T *)P->part_slices);
         return;
     }
     launch_tiles(P, op, P->tr, P->rp, P->ci, v);
@@ -675,8 +705,7 @@ static int launch_product(dpdlp_problem *P, bool transpose, const Op &op, const 
         PartialOp<double> po;
         po.v = in; po.partial = (double *)P->part_slices; po.partials = nullptr;
         launch_tiles(P, po, ss.ts, ss.ptr, ss.idx, ss.val);
-        hipLaunchKernelGGL(k_combine<Op>, dim3(nblk(nseg)), dim3(kBlock), 0, P->s, op, nseg, ss.S,
-                           (const double *)P->part_slices, ss.mask, ss.cbase, ss.G);
+        launch_combine(P, op, nseg, ss, (const double *)P->part_slices);
         return (int)nblk(nseg);
     }
     if (transpose) launch_tiles(P, op, P->tc, P->cp, P->ri, P->vt);
@@ -703,9 +732,7 @@ static void launch_checks(dpdlp_problem *P, const double *xh, const double *dx, 
             po.v = xh; po.v2 = dx; po.partial = (double *)P->part_slices; po.G = P->sr.G;
             po.partials = nullptr;
             launch_tiles(P, po, P->sr.ts, P->sr.ptr, P->sr.idx, P->sr.val);
-            hipLaunchKernelGGL(k_combine<CheckRowOp<TA>>, dim3(nblk(P->m)), dim3(kBlock), 0, P->s, op,
-                               P->m, P->sr.S, (const double *)P->part_slices, P->sr.mask,
-                               P->sr.cbase, P->sr.G);
+            launch_combine(P, op, P->m, P->sr, (const double *)P->part_slices);
             P->chk_nr = nblk(P->m);
         } else {
             launch_tiles(P, op, P->tr, P->rp, P->ci, P->v);
@@ -722,9 +749,7 @@ static void launch_checks(dpdlp_problem *P, const double *xh, const double *dx, 
             PartialOp<double> po;
             po.v = yh; po.partial = (double *)P->part_slices; po.partials = nullptr;
             launch_tiles(P, po, P->sc.ts, P->sc.ptr, P->sc.idx, P->sc.val);
-            hipLaunchKernelGGL(k_combine<CheckColOp<TA>>, dim3(nblk(P->n)), dim3(kBlock), 0, P->s, op,
-                               P->n, P->sc.S, (const double *)P->part_slices, P->sc.mask,
-                               P->sc.cbase, P->sc.G);
+            launch_combine(P, op, P->n, P->sc, (const double *)P->part_slices);
             P->chk_nc = nblk(P->n);
         } else {
             launch_tiles(P, op, P->tc, P->cp, P->ri, P->vt);
@@ -768,6 +793,7 @@ static int build_tileset(dpdlp_problem *P, const hvec<int32_t> &ptr, int32_t nse
         if (t.npieces > 0 && t.piece == 0) sp.push_back(SplitSeg{t.seg_begin, i, t.npieces, t.slice});
     }
     ts.nsplit = (int)sp.size();
+    choose_sum_widths(host_tiles, ptr.data());
     CHK(dalloc(P, &ts.d, host_tiles.size()));
     CHK(upload(P, ts.d, host_tiles.data(), host_tiles.size() * sizeof(Tile)));
     if (ts.nsplit) {

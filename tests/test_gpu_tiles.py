@@ -38,3 +38,21 @@ def test_tile_sizes_around_the_instantiations(D, O, tile_nnz):  # noqa: F811
 @pytest.mark.parametrize("mean", [1, 2, 4, 8, 16, 40])
 def test_segment_reduction_widths(D, O, mean):  # noqa: F811
     fixed_run(D, O, ragged_lp(mean, 50 + mean), 130)
+
+
+@pytest.mark.parametrize("long_len", [65, 700, 2040])
+def test_long_segments_among_short_ones(D, O, long_len):  # noqa: F811
+    """Tiles that mix rows of 1 to 3 nonzeros with long rows (the summing
+    width is chosen from the longest lanes of the tile's waves)."""
+    rng = np.random.default_rng(long_len)
+    m, n = 1500, 2100
+    deg = rng.integers(1, 4, size=m)
+    deg[rng.choice(m, size=9, replace=False)] = long_len
+    cols = np.concatenate([np.sort(rng.choice(n, size=d, replace=False)) for d in deg])
+    rp = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    val = rng.standard_normal(cols.size)
+    x = rng.uniform(0, 1, n)
+    ax = np.bincount(np.repeat(np.arange(m), deg), weights=val * x[cols], minlength=m)
+    lp = lpgen.LP(m, n, rp, cols.astype(np.int32), val, rng.standard_normal(n), ax - 0.1,
+                  np.full(m, np.inf), np.zeros(n), np.full(n, 2.0), name=f"long{long_len}")
+    fixed_run(D, O, lp, 130, gpu_kw=dict(tile_nnz=2048))
