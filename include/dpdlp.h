@@ -404,7 +404,8 @@ int dpdlp_gnn_backward(dpdlp_gnn *gnn, const double *x_target, const double *y_t
  * BF16 copies used by the forward pass.                                   */
 int dpdlp_gnn_adam_step(dpdlp_gnn *gnn, double lr, double beta1, double beta2, double eps,
                         void *stream);
-/* The network's MFMA GEMM kernel alone (tests): C [M x Nc] FP32 (row stride
+/* An MFMA GEMM with general strides alone (tests; the network's own
+ * products take packed weights): C [M x Nc] FP32 (row stride
  * ldc) = A [M x K] B [K x Nc] with BF16 bit patterns, A(i,k) at
  * A[i*a_rs + k*a_cs], B(k,j) at B[k*b_rs + j*b_cs].  Device pointers.    */
 int dpdlp_gnn_gemm_test(const uint16_t *A, long a_rs, long a_cs, const uint16_t *B, long b_rs,

@@ -24,8 +24,10 @@
 
 #include <cmath>
 #include <cstring>
+#include <algorithm>
 #include <memory>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "dpdlp_internal.h"
@@ -50,41 +52,35 @@ __device__ __forceinline__ bf16 f2bf(float f)
 }
 __device__ __forceinline__ float bf2f(bf16 h) { return __uint_as_float(((uint32_t)h) << 16); }
 
-enum { G_RELU = 1, G_OUT_BF16 = 2, G_ACCUM = 4 };
-
-// C[M x Nc] = A[M x K] B[K x Nc] on the matrix cores (v_mfma_f32_16x16x16_bf16).
-// A(i,k) = A[i*a_rs + k*a_cs], B(k,j) = B[k*b_rs + j*b_cs]: the strides cover
-// X W, dZ W^T and X^T dZ without transposed copies.  A workgroup (4 wave64)
-// owns a 64 x 64 output tile, each wave a 32 x 32 sub-tile (2 x 2 MFMA
-// tiles); 64 x 32 slices of A and B are staged in LDS per K step.  blockIdx.z
-// selects a K chunk [z*kc, (z+1)*kc) whose result goes to C + z*c_zs (split K;
-// the chunks are added afterwards in chunk order).
+// C[M x Nc] = A[M x K] B[K x Nc] with general strides, for dpdlp_gnn_gemm_test
+// only: A(i,k) = A[i*a_rs + k*a_cs], B(k,j) = B[k*b_rs + j*b_cs].  A workgroup
+// (4 wave64) owns a 64 x 64 output tile, each wave a 32 x 32 sub-tile (2 x 2
+// MFMA tiles); 64 x 32 slices of A and B are staged in LDS per K step.
 __global__ __launch_bounds__(256) void k_gemm(const bf16 *__restrict__ A, long a_rs, long a_cs,
                                               const bf16 *__restrict__ B, long b_rs, long b_cs,
-                                              void *__restrict__ C, long ldc, long c_zs, int M,
-                                              int Nc, int K, int kc, int flags)
+                                              float *__restrict__ C, long ldc, int M, int Nc,
+                                              int K)
 {
     __shared__ bf16 As[64][40];
     __shared__ bf16 Bs[64][40];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int bm = blockIdx.x * 64, bn = blockIdx.y * 64;
-    const int k0 = blockIdx.z * kc, k1 = min(K, k0 + kc);
     const int wm = (w & 1) * 32, wn = (w >> 1) * 32;
     float4v acc[2][2];
     for (int a = 0; a < 2; ++a)
         for (int b = 0; b < 2; ++b) acc[a][b] = float4v{0.f, 0.f, 0.f, 0.f};
-    for (int kk = k0; kk < k1; kk += 32) {
+    for (int kk = 0; kk < K; kk += 32) {
         for (int e = tid; e < 64 * 32; e += 256) {
             int i, k;
             if (a_cs == 1) { i = e >> 5; k = e & 31; } else { i = e & 63; k = e >> 6; }
             const int gi = bm + i, gk = kk + k;
-            As[i][k] = (gi < M && gk < k1) ? A[(long)gi * a_rs + (long)gk * a_cs] : (bf16)0;
+            As[i][k] = (gi < M && gk < K) ? A[(long)gi * a_rs + (long)gk * a_cs] : (bf16)0;
         }
         for (int e = tid; e < 64 * 32; e += 256) {
             int j, k;
             if (b_cs == 1) { j = e & 63; k = e >> 6; } else { j = e >> 5; k = e & 31; }
             const int gj = bn + j, gk = kk + k;
-            Bs[j][k] = (gj < Nc && gk < k1) ? B[(long)gk * b_rs + (long)gj * b_cs] : (bf16)0;
+            Bs[j][k] = (gj < Nc && gk < K) ? B[(long)gk * b_rs + (long)gj * b_cs] : (bf16)0;
         }
         __syncthreads();
 #pragma unroll
@@ -105,8 +101,6 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16 *__restrict__ A, long a
         }
         __syncthreads();
     }
-    float *C32 = (float *)C;
-    bf16 *C16 = (bf16 *)C;
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -115,65 +109,427 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16 *__restrict__ A, long a
             for (int v = 0; v < 4; ++v) {
                 const int i = bm + wm + a * 16 + 4 * (lane >> 4) + v;
                 const int j = bn + wn + b * 16 + (lane & 15);
-                if (i >= M || j >= Nc) continue;
-                const long off = (long)blockIdx.z * c_zs + (long)i * ldc + j;
-                float r = acc[a][b][v];
-                if (flags & G_ACCUM) r += (flags & G_OUT_BF16) ? bf2f(C16[off]) : C32[off];
-                if (flags & G_RELU) r = fmaxf(r, 0.f);
-                if (flags & G_OUT_BF16) C16[off] = f2bf(r);
-                else C32[off] = r;
+                if (i < M && j < Nc) C[(long)i * ldc + j] = acc[a][b][v];
             }
 }
 
-// out[e] (+)= sum_z part[z * stride + e], z in chunk order.
-__global__ void k_sum_chunks(const float *__restrict__ part, long stride, int nz, float *out, long n,
-                             int accum)
+// ---- the network's matrix products -----------------------------------------
+// All of them use v_mfma_f32_16x16x16_bf16 in ascending steps of 16 along the
+// contraction, with the operands swapped (the weights or dZ as A): a lane then
+// holds 4 consecutive features of one node, one 8- or 16-byte store.
+//
+// A fragment is 64 lanes x 4 BF16: lane (g, i) = (lane >> 4, lane & 15) holds
+// the elements k = 4 g .. 4 g + 3 of row or column i.  Weights are kept packed
+// in fragments, twice: for X W (fragment [k step][column tile]) and, for the
+// 256 x 128 ones, for dZ W^T (fragment [feature step][row tile]).
+
+__device__ __forceinline__ float4v mfma(uint2 a, uint2 b, float4v c)
 {
-    long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n) return;
-    float s = 0.f;
-    for (int z = 0; z < nz; ++z) s += part[(long)z * stride + e];
-    out[e] = accum ? out[e] + s : s;
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4v, a),
+                                                     __builtin_bit_cast(short4v, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ uint2 pack4(const float *f)
+{
+    return make_uint2((uint32_t)f2bf(f[0]) | ((uint32_t)f2bf(f[1]) << 16),
+                      (uint32_t)f2bf(f[2]) | ((uint32_t)f2bf(f[3]) << 16));
+}
+// relu of 4 accumulators as BF16
+__device__ __forceinline__ uint2 relu4(float4v c)
+{
+    const float f[4] = {fmaxf(c[0], 0.f), fmaxf(c[1], 0.f), fmaxf(c[2], 0.f), fmaxf(c[3], 0.f)};
+    return pack4(f);
 }
 
-// out[s, :] (+)= sum_{p in segment s} a_p in[idx_p, :]; one wave per segment,
-// each lane two of the 128 features; FP32 accumulation in stored order.
-template <typename TI, typename TO>
-__global__ __launch_bounds__(256) void k_spmm(const int *__restrict__ ptr, const int *__restrict__ idx,
-                                              const float *__restrict__ val, int nseg,
-                                              const TI *__restrict__ in, long in_ld,
-                                              TO *__restrict__ out, long out_ld, int accum)
+// Where element (k, j) of a matrix with 16 ks rows and 128 columns goes in
+// its two packed copies.
+__device__ __forceinline__ long packed_fwd(int k, int j)
 {
-    const int seg = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (seg >= nseg) return;
-    float a0 = 0.f, a1 = 0.f;
-    const int pe = ptr[seg + 1];
-    for (int p = ptr[seg]; p < pe; ++p) {
-        const int j = idx[p];
-        const float a = val[p];
-        float h0, h1;
-        if constexpr (sizeof(TI) == 2) {
-            const uint32_t u = *(const uint32_t *)((const bf16 *)in + (long)j * in_ld + 2 * lane);
-            h0 = bf2f((bf16)(u & 0xffffu));
-            h1 = bf2f((bf16)(u >> 16));
-        } else {
-            const float2 f = *(const float2 *)((const float *)in + (long)j * in_ld + 2 * lane);
-            h0 = f.x; h1 = f.y;
+    return ((long)((k >> 4) * 8 + (j >> 4)) * 64 + ((k & 15) >> 2) * 16 + (j & 15)) * 4 + (k & 3);
+}
+__device__ __forceinline__ long packed_bwd(int k, int j)
+{
+    return ((long)((j >> 4) * 16 + (k >> 4)) * 64 + ((j & 15) >> 2) * 16 + (k & 15)) * 4 + (j & 3);
+}
+
+// Input embedding H = relu(X W), X with 16 features: one MFMA per 16 nodes and
+// 16 features; column nodes first, then row nodes.
+__global__ __launch_bounds__(256) void k_embed(int n, const bf16 *__restrict__ Xc,
+                                               const bf16 *__restrict__ Wc, bf16 *__restrict__ Hc,
+                                               int m, const bf16 *__restrict__ Xr,
+                                               const bf16 *__restrict__ Wr, bf16 *__restrict__ Hr)
+{
+    const int nbx = (n + 63) / 64;
+    const bool col = (int)blockIdx.x < nbx;
+    const int N = col ? n : m;
+    const uint2 *X = (const uint2 *)(col ? Xc : Xr), *W = (const uint2 *)(col ? Wc : Wr);
+    bf16 *H = col ? Hc : Hr;
+    const int lane = threadIdx.x & 63, g = lane >> 4;
+    const int row = ((col ? blockIdx.x : blockIdx.x - nbx) * 4 + (threadIdx.x >> 6)) * 16 + (lane & 15);
+    const uint2 x = X[(long)min(row, N - 1) * (kF / 4) + g];
+    uint2 w[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) w[t] = W[t * 64 + lane];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const float4v c = mfma(w[t], x, float4v{0.f, 0.f, 0.f, 0.f});
+        if (row < N) *(uint2 *)(H + (long)row * 2 * kH + t * 16 + 4 * g) = relu4(c);
+    }
+}
+
+// Layer update out = relu(IN W), IN with 256 features.  Bound by memory: 768
+// bytes per node.  Persistent workgroups hold the packed W (64 KB) in LDS; a
+// wave takes 16 nodes at a time and has the next 16 nodes' loads in flight
+// while it multiplies.
+__global__ __launch_bounds__(256, 2) void k_dense(int N, const bf16 *__restrict__ IN,
+                                                  const bf16 *__restrict__ W, bf16 *__restrict__ out,
+                                                  long ld)
+{
+    __shared__ uint2 sW[16 * 8 * 64];
+    const int lane = threadIdx.x & 63, g = lane >> 4;
+    const int tiles = (N + 15) / 16, step = gridDim.x * 4;
+    int tile = blockIdx.x * 4 + (threadIdx.x >> 6);
+    auto load = [&](int t, uint2 (&x)[16]) {
+        const uint2 *p = (const uint2 *)(IN + (long)min(t * 16 + (lane & 15), N - 1) * 2 * kH) + g;
+#pragma unroll
+        for (int ks = 0; ks < 16; ++ks) x[ks] = p[ks * 4];
+    };
+    uint2 x[16];
+    load(min(tile, tiles - 1), x);
+    for (int e = threadIdx.x; e < 16 * 8 * 32; e += 256) ((uint4 *)sW)[e] = ((const uint4 *)W)[e];
+    __syncthreads();
+    for (; tile < tiles; tile += step) {
+        uint2 nx[16];
+        load(min(tile + step, tiles - 1), nx);
+        int w0 = lane;
+        asm volatile("" : "+v"(w0));      // keeps the reads of W inside the loop
+        float4v acc[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) acc[t] = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < 16; ++ks)
+#pragma unroll
+            for (int t = 0; t < 8; ++t) acc[t] = mfma(sW[(ks * 8 + t) * 64 + w0], x[ks], acc[t]);
+        const int row = tile * 16 + (lane & 15);
+        if (row < N)
+#pragma unroll
+            for (int t = 0; t < 8; ++t) *(uint2 *)(out + (long)row * ld + t * 16 + 4 * g) = relu4(acc[t]);
+#pragma unroll
+        for (int ks = 0; ks < 16; ++ks) x[ks] = nx[ks];
+    }
+}
+
+// The same update for few nodes, where a launch is one round trip: a wave
+// takes 16 nodes and 32 features and loads both operands straight into
+// registers, all at once.
+__global__ __launch_bounds__(256) void k_dense_few(int N, const bf16 *__restrict__ IN,
+                                                   const bf16 *__restrict__ W,
+                                                   bf16 *__restrict__ out, long ld)
+{
+    const int lane = threadIdx.x & 63, g = lane >> 4, t0 = (threadIdx.x >> 6) * 2;
+    const int row = blockIdx.x * 16 + (lane & 15);
+    const uint2 *p = (const uint2 *)(IN + (long)min(row, N - 1) * 2 * kH) + g;
+    uint2 x[16], w[16][2];
+#pragma unroll
+    for (int ks = 0; ks < 16; ++ks) {
+        x[ks] = p[ks * 4];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) w[ks][t] = ((const uint2 *)W)[(ks * 8 + t0 + t) * 64 + lane];
+    }
+    float4v acc[2] = {float4v{0.f, 0.f, 0.f, 0.f}, float4v{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int ks = 0; ks < 16; ++ks)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) acc[t] = mfma(w[ks][t], x[ks], acc[t]);
+    if (row < N)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+            *(uint2 *)(out + (long)row * ld + (t0 + t) * 16 + 4 * g) = relu4(acc[t]);
+}
+
+// dZ = dH * [H > 0] (the ReLU derivative on the stored output) as a BF16 pair
+// hi + lo with hi = bf16(dZ), lo = bf16(dZ - hi): the gradient products run
+// both on the matrix cores and add them in FP32 (about 16 mantissa bits).
+__device__ __forceinline__ void relu_grad(float4 d, uint2 h, uint2 &hi, uint2 &lo)
+{
+    const float f[4] = {d.x, d.y, d.z, d.w};
+    const uint32_t hb[4] = {h.x & 0xffffu, h.x >> 16, h.y & 0xffffu, h.y >> 16};
+    float gr[4], res[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) gr[v] = bf2f((bf16)hb[v]) > 0.f ? f[v] : 0.f;
+    hi = pack4(gr);
+    const uint32_t ib[4] = {hi.x & 0xffffu, hi.x >> 16, hi.y & 0xffffu, hi.y >> 16};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) res[v] = gr[v] - bf2f((bf16)ib[v]);
+    lo = pack4(res);
+}
+
+// Data gradient of a layer update: dZ from dH and the stored output, written
+// out for the weight gradient, and [dH, dS] = dZ W^T (256 features, FP32; the
+// left half replaces dH in place, each wave reading its nodes before it
+// writes them).  Bound by memory: 2304 bytes per node.  Persistent workgroups
+// with the packed W^T (64 KB) in LDS, as in k_dense.
+__global__ __launch_bounds__(256, 2) void k_dgrad(int N, float *dH, const bf16 *__restrict__ H,
+                                                  long hld, const bf16 *__restrict__ Wt,
+                                                  bf16 *__restrict__ dZ, bf16 *__restrict__ dZlo,
+                                                  float *__restrict__ dS)
+{
+    __shared__ uint2 sW[8 * 16 * 64];
+    const int lane = threadIdx.x & 63, g = lane >> 4;
+    const int tiles = (N + 15) / 16, step = gridDim.x * 4;
+    for (int e = threadIdx.x; e < 8 * 16 * 32; e += 256) ((uint4 *)sW)[e] = ((const uint4 *)Wt)[e];
+    __syncthreads();
+    for (int tile = blockIdx.x * 4 + (threadIdx.x >> 6); tile < tiles; tile += step) {
+        const int row = tile * 16 + (lane & 15);
+        const long r = min(row, N - 1);
+        int w0 = lane;
+        asm volatile("" : "+v"(w0));      // keeps the reads of W inside the loop
+        float4 d[8];
+        uint2 h[8], hi[8], lo[8];
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+            d[ks] = *(const float4 *)(dH + r * kH + ks * 16 + 4 * g);
+            h[ks] = *(const uint2 *)(H + r * hld + ks * 16 + 4 * g);
         }
-        a0 += a * h0;
-        a1 += a * h1;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+            relu_grad(d[ks], h[ks], hi[ks], lo[ks]);
+            if (row < N) {
+                *(uint2 *)(dZ + r * kH + ks * 16 + 4 * g) = hi[ks];
+                *(uint2 *)(dZlo + r * kH + ks * 16 + 4 * g) = lo[ks];
+            }
+        }
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            float4v ah[8], al[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) ah[t] = al[t] = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks)
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const uint2 w = sW[(ks * 16 + half * 8 + t) * 64 + w0];
+                    ah[t] = mfma(w, hi[ks], ah[t]);
+                    al[t] = mfma(w, lo[ks], al[t]);
+                }
+            float *o = (half == 0 ? dH : dS) + r * kH + 4 * g;
+            if (row < N)
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const float4v c = al[t] + ah[t];
+                    *(float4 *)(o + t * 16) = make_float4(c[0], c[1], c[2], c[3]);
+                }
+        }
     }
-    const long o = (long)seg * out_ld + 2 * lane;
-    if constexpr (sizeof(TO) == 2) {
-        bf16 *po = (bf16 *)out + o;
-        if (accum) { a0 += bf2f(po[0]); a1 += bf2f(po[1]); }
-        po[0] = f2bf(a0); po[1] = f2bf(a1);
-    } else {
-        float *po = (float *)out + o;
-        if (accum) { a0 += po[0]; a1 += po[1]; }
-        po[0] = a0; po[1] = a1;
+}
+
+// Weight gradient partials A^T dZ over chunks of kKC nodes, for both halves of
+// dZ: part[(2 z + half) M 128 + ...].  A workgroup owns 16 MT features of A and
+// 64 of dZ and walks its chunk in steps of 64 nodes: 4 nodes x 4 features per
+// thread and operand are transposed in registers into fragments in LDS, and
+// the next step's loads are in flight meanwhile.  The tiles of one chunk run
+// on one XCD, whose L2 then serves the chunk's rows to all of them.
+template <int MT>
+__global__ __launch_bounds__(256) void k_wgrad(const bf16 *__restrict__ A, long a_ld, int M,
+                                               const bf16 *__restrict__ dZ,
+                                               const bf16 *__restrict__ dZlo, int K, int nz,
+                                               float *__restrict__ part)
+{
+    constexpr int MW = MT == 4 ? 2 : 1, NW = MT == 4 ? 2 : 1;      // tiles of one wave
+    __shared__ uint2 sD[2][2][4][4][64];
+    __shared__ uint2 sA[2][4][MT][64];
+    const int tiles = M / (16 * MT) * 2;
+    const int tile = (blockIdx.x >> 3) % tiles;
+    const int z = (blockIdx.x >> 3) / tiles * 8 + (blockIdx.x & 7);
+    if (z >= nz) return;
+    const int fb = (tile >> 1) * 16 * MT, jb = (tile & 1) * 64;
+    const int k0 = z * kKC, k1 = min(K, k0 + kKC);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int q = tid >> 4, fg = tid & 15;
+    const bool loads_a = MT == 4 || fg < 4 * MT;
+    const int mt0 = MT == 4 ? (wave & 1) * 2 : 0, nt0 = MT == 4 ? (wave >> 1) * 2 : wave;
+    uint2 rd[2][4], ra[4] = {};
+    auto load = [&](int k) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = k + 4 * q + r;
+            const bool in = row < k1;
+            const long o = (long)(in ? row : k0) * kH + jb + 4 * fg;
+            const uint2 none = make_uint2(0, 0);
+            rd[0][r] = in ? *(const uint2 *)(dZ + o) : none;
+            rd[1][r] = in ? *(const uint2 *)(dZlo + o) : none;
+            if (loads_a) ra[r] = in ? *(const uint2 *)(A + (long)row * a_ld + fb + 4 * fg) : none;
+        }
+    };
+    // 4 nodes x 4 features -> the 4 features' fragments, which are neighbours
+    auto put = [&](uint2 (&t)[64], const uint2 (&v)[4]) {
+        uint4 *o = (uint4 *)&t[(q & 3) * 16 + (fg & 3) * 4];
+        const uint32_t lo = 0xffffu, hi = 0xffff0000u;
+        o[0] = make_uint4((v[0].x & lo) | (v[1].x << 16), (v[2].x & lo) | (v[3].x << 16),
+                          (v[0].x >> 16) | (v[1].x & hi), (v[2].x >> 16) | (v[3].x & hi));
+        o[1] = make_uint4((v[0].y & lo) | (v[1].y << 16), (v[2].y & lo) | (v[3].y << 16),
+                          (v[0].y >> 16) | (v[1].y & hi), (v[2].y >> 16) | (v[3].y & hi));
+    };
+    float4v acc[2][NW][MW];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int b = 0; b < NW; ++b)
+#pragma unroll
+            for (int a = 0; a < MW; ++a) acc[h][b][a] = float4v{0.f, 0.f, 0.f, 0.f};
+    load(k0);
+    int buf = 0;
+    for (int k = k0; k < k1; k += 64, buf ^= 1) {
+        put(sD[buf][0][q >> 2][fg >> 2], rd[0]);
+        put(sD[buf][1][q >> 2][fg >> 2], rd[1]);
+        if (loads_a) put(sA[buf][q >> 2][fg >> 2], ra);
+        if (k + 64 < k1) load(k + 64);
+        __syncthreads();      // one barrier per step: the buffers alternate
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            uint2 fa[MW], fd[2][NW];
+#pragma unroll
+            for (int a = 0; a < MW; ++a) fa[a] = sA[buf][ks][mt0 + a][lane];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int b = 0; b < NW; ++b) fd[h][b] = sD[buf][h][ks][nt0 + b][lane];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int b = 0; b < NW; ++b)
+#pragma unroll
+                    for (int a = 0; a < MW; ++a) acc[h][b][a] = mfma(fd[h][b], fa[a], acc[h][b][a]);
+        }
     }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int b = 0; b < NW; ++b)
+#pragma unroll
+            for (int a = 0; a < MW; ++a) {
+                const float4v c = acc[h][b][a];
+                const long f = fb + (mt0 + a) * 16 + (lane & 15);
+                float *o = part + ((long)(2 * z + h) * M + f) * kH + jb + (nt0 + b) * 16 + 4 * (lane >> 4);
+                *(float4 *)o = make_float4(c[0], c[1], c[2], c[3]);
+            }
+}
+
+// out = (sum of the hi partials in chunk order) + (sum of the lo partials).
+__global__ __launch_bounds__(256) void k_sum_wgrad(const float *__restrict__ part, long stride,
+                                                   int nz, float *__restrict__ out)
+{
+    const long e = (long)blockIdx.x * 256 + threadIdx.x;
+    if (e >= stride) return;
+    float s = 0.f, t = 0.f;
+    int z = 0;
+    for (; z + 8 <= nz; z += 8) {
+        float a[8], b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            a[u] = part[(long)(2 * (z + u)) * stride + e];
+            b[u] = part[(long)(2 * (z + u) + 1) * stride + e];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) { s += a[u]; t += b[u]; }
+    }
+    for (; z < nz; ++z) {
+        s += part[(long)(2 * z) * stride + e];
+        t += part[(long)(2 * z + 1) * stride + e];
+    }
+    out[e] = s + t;
+}
+
+// ---- the sparse products ---------------------------------------------------------
+// The value of lane N of each 16 lanes.
+template <int N>
+__device__ __forceinline__ uint32_t row_bcast(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + N, 0xf, 0xf, true);
+}
+
+// out[s, :] (+)= sum_{p in segment s} a_p in[idx_p, :], FP32 accumulation in
+// stored order.  LPS lanes own a segment and 16 bytes of every gathered row
+// (16 lanes: BF16 rows of 256 bytes; 32 lanes: FP32 rows of 512 bytes); they
+// read 16 (index, value) pairs at once, hand them out by lane permutations and
+// keep 8 gathers in flight.
+template <int LPS, typename Fma>
+__device__ __forceinline__ void spmm_segment(const int *__restrict__ idx, const float *__restrict__ val,
+                                             int p, int pe, const char *__restrict__ in, long in_bytes,
+                                             Fma &&fma8)
+{
+    const int l = threadIdx.x & 15;
+    in += 16 * (threadIdx.x & (LPS - 1));
+    while (__any(p < pe)) {
+        uint32_t j = 0, a = 0;
+        if (p + l < pe) {
+            j = (uint32_t)idx[p + l];
+            a = __float_as_uint(val[p + l]);
+        }
+        auto half = [&](auto h) {
+            constexpr int B = decltype(h)::value * 8;
+            if (!__any(p + B < pe)) return;
+            const uint32_t jb[8] = {row_bcast<B>(j), row_bcast<B + 1>(j), row_bcast<B + 2>(j),
+                                    row_bcast<B + 3>(j), row_bcast<B + 4>(j), row_bcast<B + 5>(j),
+                                    row_bcast<B + 6>(j), row_bcast<B + 7>(j)};
+            const uint32_t ab[8] = {row_bcast<B>(a), row_bcast<B + 1>(a), row_bcast<B + 2>(a),
+                                    row_bcast<B + 3>(a), row_bcast<B + 4>(a), row_bcast<B + 5>(a),
+                                    row_bcast<B + 6>(a), row_bcast<B + 7>(a)};
+            uint4 r[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) r[u] = *(const uint4 *)(in + (long)jb[u] * in_bytes);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (p + B + u < pe) fma8(__uint_as_float(ab[u]), r[u]);
+        };
+        half(std::integral_constant<int, 0>{});
+        half(std::integral_constant<int, 1>{});
+        p += 16;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_spmm_bf16(const int *__restrict__ ptr,
+                                                   const int *__restrict__ idx,
+                                                   const float *__restrict__ val, int nseg,
+                                                   const bf16 *__restrict__ in, long in_ld,
+                                                   bf16 *__restrict__ out, long out_ld)
+{
+    const int seg = blockIdx.x * 16 + (threadIdx.x >> 4);
+    const bool on = seg < nseg;
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    spmm_segment<16>(idx, val, on ? ptr[seg] : 0, on ? ptr[seg + 1] : 0, (const char *)in,
+                     in_ld * sizeof(bf16), [&](float a, uint4 r) {
+                         const uint32_t u[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+                         for (int q = 0; q < 4; ++q) {
+                             acc[2 * q] += a * bf2f((bf16)(u[q] & 0xffffu));
+                             acc[2 * q + 1] += a * bf2f((bf16)(u[q] >> 16));
+                         }
+                     });
+    if (!on) return;
+    const uint2 lo = pack4(acc), hi = pack4(acc + 4);
+    *(uint4 *)(out + (long)seg * out_ld + 8 * (threadIdx.x & 15)) = make_uint4(lo.x, lo.y, hi.x, hi.y);
+}
+
+// out += (the gradient products), rows of 128 FP32
+__global__ __launch_bounds__(256) void k_spmm_f32_add(const int *__restrict__ ptr,
+                                                      const int *__restrict__ idx,
+                                                      const float *__restrict__ val, int nseg,
+                                                      const float *__restrict__ in,
+                                                      float *__restrict__ out)
+{
+    const int seg = blockIdx.x * 8 + (threadIdx.x >> 5);
+    const bool on = seg < nseg;
+    float4 *o = (float4 *)(out + (long)(on ? seg : 0) * kH) + (threadIdx.x & 31);
+    const float4 old = *o;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    spmm_segment<32>(idx, val, on ? ptr[seg] : 0, on ? ptr[seg + 1] : 0, (const char *)in,
+                     kH * sizeof(float), [&](float a, uint4 r) {
+                         acc[0] += a * __uint_as_float(r.x);
+                         acc[1] += a * __uint_as_float(r.y);
+                         acc[2] += a * __uint_as_float(r.z);
+                         acc[3] += a * __uint_as_float(r.w);
+                     });
+    if (on) *o = make_float4(acc[0] + old.x, acc[1] + old.y, acc[2] + old.z, acc[3] + old.w);
 }
 
 __global__ void k_d2f(const double *__restrict__ a, float *__restrict__ b, long n)
@@ -181,140 +537,234 @@ __global__ void k_d2f(const double *__restrict__ a, float *__restrict__ b, long 
     long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) b[i] = (float)a[i];
 }
-__global__ void k_f2bf(const float *__restrict__ a, bf16 *__restrict__ b, long n)
+// Parameter i's places in the packed BF16 copies: both matrices' layouts keep
+// a matrix inside its own range of the parameter vector; the heads stay FP32.
+__device__ __forceinline__ void store_packed(long i, long heads, float v, bf16 *wf, bf16 *wt)
 {
-    long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) b[i] = f2bf(a[i]);
+    if (i >= heads) return;
+    const bf16 h = f2bf(v);
+    const long embed = 2L * kF * kH;
+    if (i < embed) {
+        const int e = (int)(i % (kF * kH));
+        wf[i - e + packed_fwd(e / kH, e % kH)] = h;
+    } else {
+        const int e = (int)((i - embed) % (2 * kH * kH));
+        wf[i - e + packed_fwd(e / kH, e % kH)] = h;
+        wt[i - e + packed_bwd(e / kH, e % kH)] = h;
+    }
+}
+__global__ void k_pack(const float *__restrict__ w, bf16 *__restrict__ wf, bf16 *__restrict__ wt,
+                       long heads)
+{
+    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < heads) store_packed(i, heads, w[i], wf, wt);
 }
 
-// Column features (permuted order, scaled space; see dpdlp.h):
-//   [c~, c~ - c~ref, x~ref, has_lo, has_hi, lo~ or 0, hi~ or 0, 1, 0 ...]
-__global__ void k_feat_col(int n, const int *perm, const double *dc, const double *c,
-                           const double *cref, const double *xref, const double *vlo0,
-                           const double *vhi0, bf16 *X, float *xref_s)
+// Features (permuted order, scaled space; see dpdlp.h), column nodes first:
+//   column [c~, c~ - c~ref, x~ref, has_lo, has_hi, lo~ or 0, hi~ or 0, 1, 0 ...]
+//   row    [b~, b~ - b~ref, y~ref, is_eq, has_lo, has_hi, 0, 1, 0 ...],
+//          b = finite lo, else finite hi, else 0
+struct FeatArgs {
+    int n, m;
+    const int *pc, *pr;
+    const double *dc, *dr, *c, *cref, *xref, *vlo0, *vhi0, *lo, *hi, *bref, *yref;
+    bf16 *Xc, *Xr;
+    float *xref_s, *yref_s;
+};
+__global__ __launch_bounds__(256) void k_features(FeatArgs a)
 {
-    int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
-    const int o = perm[j];
-    const double d = dc[j];
-    const double lo = vlo0[j], hi = vhi0[j];
+    const int nbx = (a.n + 255) / 256;
+    const bool col = (int)blockIdx.x < nbx;
+    const int j = (col ? blockIdx.x : blockIdx.x - nbx) * 256 + threadIdx.x;
+    if (j >= (col ? a.n : a.m)) return;
     float f[kF] = {0};
-    f[0] = (float)(d * c[o]);
-    f[1] = (float)(d * (c[o] - cref[o]));
-    const double xr = xref[o] / d;
-    f[2] = (float)xr;
-    f[3] = isfinite(lo) ? 1.f : 0.f;
-    f[4] = isfinite(hi) ? 1.f : 0.f;
-    f[5] = isfinite(lo) ? (float)fmin(fmax(lo / d, -1e4), 1e4) : 0.f;
-    f[6] = isfinite(hi) ? (float)fmin(fmax(hi / d, -1e4), 1e4) : 0.f;
+    if (col) {
+        const int o = a.pc[j];
+        const double d = a.dc[j];
+        const double lo = a.vlo0[j], hi = a.vhi0[j];
+        f[0] = (float)(d * a.c[o]);
+        f[1] = (float)(d * (a.c[o] - a.cref[o]));
+        f[2] = (float)(a.xref[o] / d);
+        f[3] = isfinite(lo) ? 1.f : 0.f;
+        f[4] = isfinite(hi) ? 1.f : 0.f;
+        f[5] = isfinite(lo) ? (float)fmin(fmax(lo / d, -1e4), 1e4) : 0.f;
+        f[6] = isfinite(hi) ? (float)fmin(fmax(hi / d, -1e4), 1e4) : 0.f;
+        a.xref_s[j] = f[2];
+    } else {
+        const int o = a.pr[j];
+        const double d = a.dr[j];
+        const double l = a.lo[o], h = a.hi[o];
+        const double b = isfinite(l) ? l : (isfinite(h) ? h : 0.0);
+        f[0] = (float)(d * b);
+        f[1] = (float)(d * (b - a.bref[o]));
+        f[2] = (float)(a.yref[o] / d);
+        f[3] = (isfinite(l) && isfinite(h) && l == h) ? 1.f : 0.f;
+        f[4] = isfinite(l) ? 1.f : 0.f;
+        f[5] = isfinite(h) ? 1.f : 0.f;
+        a.yref_s[j] = f[2];
+    }
     f[7] = 1.f;
-    for (int q = 0; q < kF; ++q) X[(long)j * kF + q] = f2bf(f[q]);
-    xref_s[j] = (float)xr;
-}
-// Row features: b = finite lo, else finite hi, else 0;
-//   [b~, b~ - b~ref, y~ref, is_eq, has_lo, has_hi, 0, 1, 0 ...]
-__global__ void k_feat_row(int m, const int *perm, const double *dr, const double *lo,
-                           const double *hi, const double *bref, const double *yref, bf16 *X,
-                           float *yref_s)
-{
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= m) return;
-    const int o = perm[i];
-    const double d = dr[i];
-    const double l = lo[o], h = hi[o];
-    const double b = isfinite(l) ? l : (isfinite(h) ? h : 0.0);
-    float f[kF] = {0};
-    f[0] = (float)(d * b);
-    f[1] = (float)(d * (b - bref[o]));
-    const double yr = yref[o] / d;
-    f[2] = (float)yr;
-    f[3] = (isfinite(l) && isfinite(h) && l == h) ? 1.f : 0.f;
-    f[4] = isfinite(l) ? 1.f : 0.f;
-    f[5] = isfinite(h) ? 1.f : 0.f;
-    f[7] = 1.f;
-    for (int q = 0; q < kF; ++q) X[(long)i * kF + q] = f2bf(f[q]);
-    yref_s[i] = (float)yr;
+    uint2 *X = (uint2 *)((col ? a.Xc : a.Xr) + (long)j * kF);
+#pragma unroll
+    for (int q = 0; q < kF / 4; ++q) X[q] = pack4(f + 4 * q);
 }
 
-// pred_j = ref_j + sum_f H[j, f] w[f]   (sequential over f)
-__global__ void k_head(int n, const bf16 *__restrict__ Hl, long ld, const float *__restrict__ w,
-                       const float *__restrict__ ref, float *__restrict__ pred)
+// The heads and their backward, both node kinds in one launch (kind 0:
+// columns, x; kind 1: rows, y).
+struct HeadArgs {
+    int N[2];
+    const bf16 *H[2];            // last activations, rows of 128
+    const float *w[2], *ref[2];
+    float *pred[2];
+    double *out[2];              // prediction in the original order and space, or null
+    const int *perm[2];
+    const double *scale[2];
+    const float *tgt[2];
+    float *dpred[2], *dH[2];
+    double *part[2];
+};
+__device__ __forceinline__ int head_side(const HeadArgs &a, int per, int &block)
 {
-    int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
+    const int nbx = (a.N[0] + per - 1) / per;
+    block = (int)blockIdx.x < nbx ? blockIdx.x : blockIdx.x - nbx;
+    return (int)blockIdx.x < nbx ? 0 : 1;
+}
+
+// pred_j = ref_j + sum_f H[j, f] w[f]   (sequential over f), and
+// out[perm[j]] = scale[j] pred_j  (scaled, permuted -> original: x = D_c x~,
+// y = D_r y~)
+__global__ __launch_bounds__(256) void k_head(HeadArgs a)
+{
+    int block;
+    const int k = head_side(a, 256, block);
+    const int j = block * 256 + threadIdx.x;
+    if (j >= a.N[k]) return;
+    const uint4 *h = (const uint4 *)(a.H[k] + (long)j * kH);
+    const float *w = a.w[k];
+    uint4 r[kH / 8];
+#pragma unroll
+    for (int q = 0; q < kH / 8; ++q) r[q] = h[q];
     float s = 0.f;
-    for (int f = 0; f < kH; ++f) s += bf2f(Hl[(long)j * ld + f]) * w[f];
-    pred[j] = ref[j] + s;
+#pragma unroll
+    for (int q = 0; q < kH / 8; ++q) {
+        const uint32_t u[4] = {r[q].x, r[q].y, r[q].z, r[q].w};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            s += bf2f((bf16)(u[v] & 0xffffu)) * w[q * 8 + 2 * v];
+            s += bf2f((bf16)(u[v] >> 16)) * w[q * 8 + 2 * v + 1];
+        }
+    }
+    const float p = a.ref[k][j] + s;
+    a.pred[k][j] = p;
+    if (a.out[k]) a.out[k][a.perm[k][j]] = a.scale[k][j] * (double)p;
 }
 
-// Loss gradient of the head: d_j = 2 (pred_j - target_j) / n, dH[j, f] = d_j w[f];
+// Loss gradient of the heads: d_j = 2 (pred_j - target_j) / N, dH[j, f] = d_j w[f];
 // per-block partial sums of the squared error (for the loss) go to part[block].
-__global__ __launch_bounds__(256) void k_head_bwd(int n, const float *__restrict__ pred,
-                                                  const float *__restrict__ tgt,
-                                                  const float *__restrict__ w,
-                                                  float *__restrict__ dpred,
-                                                  float *__restrict__ dH, double *part)
+__global__ __launch_bounds__(256) void k_head_bwd(HeadArgs a)
 {
     __shared__ double s[256];
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ float sd[256];
+    int block;
+    const int k = head_side(a, 256, block);
+    const int n = a.N[k], j0 = block * 256, j = j0 + threadIdx.x;
     double e2 = 0.0;
+    float d = 0.f;
     if (j < n) {
-        const float r = pred[j] - tgt[j];
+        const float r = a.pred[k][j] - a.tgt[k][j];
         e2 = (double)r * (double)r;
-        const float d = 2.f * r / (float)n;
-        dpred[j] = d;
-        for (int f = 0; f < kH; ++f) dH[(long)j * kH + f] = d * w[f];
+        d = 2.f * r / (float)n;
+        a.dpred[k][j] = d;
     }
     s[threadIdx.x] = e2;
+    sd[threadIdx.x] = d;
     __syncthreads();
+    const int f4 = threadIdx.x & 31;
+    const float4 w = ((const float4 *)a.w[k])[f4];
+    for (int i = threadIdx.x >> 5; i < 256 && j0 + i < n; i += 8) {
+        const float di = sd[i];
+        ((float4 *)(a.dH[k] + (long)(j0 + i) * kH))[f4] = make_float4(di * w.x, di * w.y, di * w.z, di * w.w);
+    }
     for (int o = 128; o > 0; o >>= 1) {
         if (threadIdx.x < o) s[threadIdx.x] += s[threadIdx.x + o];
         __syncthreads();
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = s[0];
+    if (threadIdx.x == 0) a.part[k][block] = s[0];
 }
 
-// dw[f] partials over node chunks: part[c * kH + f] = sum_{j in chunk c} d_j H[j, f]
-__global__ __launch_bounds__(kH) void k_head_wgrad(int n, int chunk, const bf16 *__restrict__ Hl,
-                                                   long ld, const float *__restrict__ d,
-                                                   float *__restrict__ part)
+// dw[f] partials over chunks of kHeadChunk nodes, in node order:
+// part[c * kH + f] = sum_{j in chunk c} d_j H[j, f]; column chunks first.  One
+// wave per chunk, two features per lane; a serial sum, so its loads go out 32
+// nodes ahead.
+constexpr int kHeadChunk = 1024;
+__global__ __launch_bounds__(64) void k_head_wgrad(HeadArgs a, float *__restrict__ part)
 {
-    const int f = threadIdx.x, c = blockIdx.x;
-    const int j0 = c * chunk, j1 = min(n, j0 + chunk);
+    int c;
+    const int k = head_side(a, kHeadChunk, c);
+    const int j0 = c * kHeadChunk, j1 = min(a.N[k], j0 + kHeadChunk);
+    const uint32_t *h = (const uint32_t *)a.H[k] + threadIdx.x;
+    const float *d = a.dpred[k];
+    float s0 = 0.f, s1 = 0.f;
+    int j = j0;
+    for (; j + 32 <= j1; j += 32) {
+        uint32_t u[32];
+#pragma unroll
+        for (int q = 0; q < 32; ++q) u[q] = h[(long)(j + q) * (kH / 2)];
+#pragma unroll
+        for (int q = 0; q < 32; ++q) {
+            s0 += d[j + q] * bf2f((bf16)(u[q] & 0xffffu));
+            s1 += d[j + q] * bf2f((bf16)(u[q] >> 16));
+        }
+    }
+    for (; j < j1; ++j) {
+        const uint32_t u = h[(long)j * (kH / 2)];
+        s0 += d[j] * bf2f((bf16)(u & 0xffffu));
+        s1 += d[j] * bf2f((bf16)(u >> 16));
+    }
+    ((float2 *)(part + (long)blockIdx.x * kH))[threadIdx.x] = make_float2(s0, s1);
+}
+// dw of both heads: the chunks added in order (block 0: columns, 1: rows).
+__global__ __launch_bounds__(kH) void k_sum_head(const float *__restrict__ part, int ncx, int ncy,
+                                                 float *__restrict__ gx, float *__restrict__ gy)
+{
+    const int c0 = blockIdx.x == 0 ? 0 : ncx, c1 = blockIdx.x == 0 ? ncx : ncx + ncy;
     float s = 0.f;
-    for (int j = j0; j < j1; ++j) s += d[j] * bf2f(Hl[(long)j * ld + f]);
-    part[(long)c * kH + f] = s;
+    int c = c0;
+    for (; c + 16 <= c1; c += 16) {
+        float a[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) a[u] = part[(long)(c + u) * kH + threadIdx.x];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) s += a[u];
+    }
+    for (; c < c1; ++c) s += part[(long)c * kH + threadIdx.x];
+    (blockIdx.x == 0 ? gx : gy)[threadIdx.x] = s;
 }
 
-// dZ = dH * [H > 0] (the ReLU derivative on the stored output), as a BF16
-// pair hi + lo with hi = bf16(dZ), lo = bf16(dZ - hi): the gradient GEMMs run
-// both on the matrix cores and add them in FP32 (about 16 mantissa bits).
-__global__ void k_relu_bwd(long rows, const float *__restrict__ dH, long dld,
-                           const bf16 *__restrict__ Hout, long hld, bf16 *__restrict__ dZ,
-                           bf16 *__restrict__ dZlo)
+// dZ pair of the embeddings (their inputs need no gradient), 4 features per
+// thread, column nodes first.
+__global__ __launch_bounds__(256) void k_relu_bwd(long n, const float *__restrict__ dHc,
+                                                  const bf16 *__restrict__ Hc, bf16 *__restrict__ dZc,
+                                                  bf16 *__restrict__ dZclo, long m,
+                                                  const float *__restrict__ dHr,
+                                                  const bf16 *__restrict__ Hr, bf16 *__restrict__ dZr,
+                                                  bf16 *__restrict__ dZrlo)
 {
-    long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= rows * kH) return;
-    const long r = e / kH, f = e % kH;
-    const float g = bf2f(Hout[r * hld + f]) > 0.f ? dH[r * dld + f] : 0.f;
-    const bf16 hi = f2bf(g);
-    dZ[r * kH + f] = hi;
-    dZlo[r * kH + f] = f2bf(g - bf2f(hi));
-}
-
-// dst[r, 0:128] = src[r, 0:128] (strided f32 copy)
-__global__ void k_copy_rows(long rows, const float *__restrict__ src, long sld, float *__restrict__ dst,
-                            long dld)
-{
-    long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= rows * kH) return;
-    const long r = e / kH, f = e % kH;
-    dst[r * dld + f] = src[r * sld + f];
+    long e = (long)blockIdx.x * 256 + threadIdx.x;
+    const bool col = e < n * 32;
+    if (!col) e -= n * 32;
+    if (!col && e >= m * 32) return;
+    const long r = e >> 5, f4 = e & 31;
+    uint2 hi, lo;
+    relu_grad(((const float4 *)(col ? dHc : dHr))[e], ((const uint2 *)((col ? Hc : Hr) + r * 2 * kH))[f4], hi, lo);
+    ((uint2 *)(col ? dZc : dZr))[e] = hi;
+    ((uint2 *)(col ? dZclo : dZrlo))[e] = lo;
 }
 
 __global__ void k_adam(long n, float *__restrict__ w, const float *__restrict__ g,
-                       float *__restrict__ m1, float *__restrict__ m2, bf16 *__restrict__ wb,
-                       float lr, float b1, float b2, float eps, float c1, float c2)
+                       float *__restrict__ m1, float *__restrict__ m2, bf16 *__restrict__ wf,
+                       bf16 *__restrict__ wt, long heads, float lr, float b1, float b2, float eps,
+                       float c1, float c2)
 {
     long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -325,38 +775,37 @@ __global__ void k_adam(long n, float *__restrict__ w, const float *__restrict__ 
     m2[i] = b;
     const float wi = w[i] - lr * (a / c1) / (sqrtf(b / c2) + eps);
     w[i] = wi;
-    wb[i] = f2bf(wi);
+    store_packed(i, heads, wi, wf, wt);
 }
 
-// out[perm[j]] = scale[j] * pred[j]  (scaled, permuted -> original; x = D_c x~,
-// y = D_r y~)
-__global__ void k_unperm_scale(int n, const float *pred, const int *perm, const double *scale,
-                               int mul, double *out)
+// Targets: original -> scaled, permuted, out[j] = x[perm[j]] / scale[j]; column
+// nodes first.
+__global__ __launch_bounds__(256) void k_targets(int n, const double *x, const int *pc,
+                                                 const double *dc, float *tx, int m, const double *y,
+                                                 const int *pr, const double *dr, float *ty)
 {
-    int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
-    out[perm[j]] = mul ? scale[j] * (double)pred[j] : (double)pred[j] / scale[j];
+    const int nbx = (n + 255) / 256;
+    const bool col = (int)blockIdx.x < nbx;
+    const int j = (col ? blockIdx.x : blockIdx.x - nbx) * 256 + threadIdx.x;
+    if (j >= (col ? n : m)) return;
+    if (col) tx[j] = (float)(x[pc[j]] / dc[j]);
+    else ty[j] = (float)(y[pr[j]] / dr[j]);
 }
-// out[j] = x[perm[j]] / scale[j]  (original -> scaled, permuted)
-__global__ void k_perm_scale(int n, const double *x, const int *perm, const double *scale, int mul,
-                             float *out)
-{
-    int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
-    out[j] = (float)(mul ? x[perm[j]] * scale[j] : x[perm[j]] / scale[j]);
-}
-__global__ __launch_bounds__(256) void k_sum_double(const double *part, int np, double *out)
+// out[b] = the sum of the b-th of two runs of partials (np0, then np1 of them)
+__global__ __launch_bounds__(256) void k_sum_double(const double *part, int np0, int np1, double *out)
 {
     __shared__ double s[256];
+    const double *p = part + (blockIdx.x == 0 ? 0 : np0);
+    const int np = blockIdx.x == 0 ? np0 : np1;
     double a = 0.0;
-    for (int i = threadIdx.x; i < np; i += 256) a += part[i];
+    for (int i = threadIdx.x; i < np; i += 256) a += p[i];
     s[threadIdx.x] = a;
     __syncthreads();
     for (int o = 128; o > 0; o >>= 1) {
         if (threadIdx.x < o) s[threadIdx.x] += s[threadIdx.x + o];
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[0] = s[0];
+    if (threadIdx.x == 0) out[blockIdx.x] = s[0];
 }
 
 }  // namespace gnn
@@ -373,7 +822,7 @@ struct dpdlp_gnn {
     std::vector<void *> mem;
     // parameters
     float *w = nullptr, *g = nullptr, *m1 = nullptr, *m2 = nullptr;
-    bf16 *wb = nullptr;
+    bf16 *wf = nullptr, *wt = nullptr;     // packed BF16 weights, for X W and for dZ W^T
     long off_cin = 0, off_rin = 0, off_wx = 0, off_wy = 0;
     std::vector<long> off_c, off_r;
     int adam_t = 0;
@@ -385,7 +834,7 @@ struct dpdlp_gnn {
     float *tx = nullptr, *ty = nullptr, *dpx = nullptr, *dpy = nullptr;
     std::vector<bf16 *> INc, INr;          // index 1..L
     bf16 *Hc_last = nullptr, *Hr_last = nullptr;
-    float *dHc = nullptr, *dHr = nullptr, *dINc = nullptr, *dINr = nullptr;
+    float *dHc = nullptr, *dHr = nullptr, *dSc = nullptr, *dSr = nullptr;
     bf16 *dZc = nullptr, *dZr = nullptr, *dZc_lo = nullptr, *dZr_lo = nullptr;
     float *wpart = nullptr;
     double *lpart = nullptr, *lsum = nullptr;
@@ -426,45 +875,46 @@ int galloc(dpdlp_gnn *G, T **p, size_t count)
 
 inline unsigned nb(long n, int b = 256) { return (unsigned)((n + b - 1) / b); }
 
-void gemm(dpdlp_gnn *G, const bf16 *A, long a_rs, long a_cs, const bf16 *B, long b_rs, long b_cs,
-          void *C, long ldc, int M, int Nc, int K, int flags)
+// persistent workgroups of the dense kernels: two per CU (their LDS), fewer
+// where there are fewer than 64 nodes for each
+unsigned dense_grid(int N) { return std::min(512u, nb(N, 64)); }
+
+// out = relu(IN W).  Below 16384 nodes one wave per 16 nodes and 32 features
+// (a launch is then one round trip, and filling 64 KB of LDS with W would be
+// the longest part of it), beyond it the persistent form.
+void dense(dpdlp_gnn *G, int N, const bf16 *IN, long off, bf16 *out, long ld)
 {
-    hipLaunchKernelGGL(k_gemm, dim3(nb(M, 64), nb(Nc, 64), 1), dim3(256), 0, G->s, A, a_rs, a_cs, B,
-                       b_rs, b_cs, C, ldc, 0L, M, Nc, K, K, flags);
+    if (N < 16384)
+        hipLaunchKernelGGL(k_dense_few, dim3(nb(N, 16)), dim3(256), 0, G->s, N, IN, G->wf + off, out, ld);
+    else
+        hipLaunchKernelGGL(k_dense, dim3(dense_grid(N)), dim3(256), 0, G->s, N, IN, G->wf + off, out, ld);
 }
 
-// weight gradient  out[M x Nc] (+)= A^T[M x K] dZ[K x Nc]  (split K, chunk order)
-void wgrad1(dpdlp_gnn *G, const bf16 *A, long a_ld, int M, const bf16 *dZ, int K, float *out,
-            int accum)
-{
-    const int nz = (K + kKC - 1) / kKC;
-    const long zs = (long)M * kH;
-    hipLaunchKernelGGL(k_gemm, dim3(nb(M, 64), nb(kH, 64), nz), dim3(256), 0, G->s, A, 1L, a_ld, dZ,
-                       (long)kH, 1L, (void *)G->wpart, (long)kH, zs, M, kH, K, kKC, 0);
-    hipLaunchKernelGGL(k_sum_chunks, dim3(nb(zs)), dim3(256), 0, G->s, G->wpart, zs, nz, out, zs,
-                       accum);
-}
-// with dZ given as the BF16 pair (hi, lo)
+// weight gradient  out[M x 128] = A^T dZ over K nodes (split K, chunk order)
+template <int MT>
 void wgrad(dpdlp_gnn *G, const bf16 *A, long a_ld, int M, const bf16 *dZ, const bf16 *dZlo, int K,
            float *out)
 {
-    wgrad1(G, A, a_ld, M, dZ, K, out, 0);
-    wgrad1(G, A, a_ld, M, dZlo, K, out, 1);
-}
-// data gradient  out[N x 256] = dZ W^T with dZ = hi + lo (FP32 output)
-void dgrad(dpdlp_gnn *G, const bf16 *dZ, const bf16 *dZlo, const bf16 *W, float *out, int N)
-{
-    gemm(G, dZ, kH, 1, W, 1, kH, out, 2 * kH, N, 2 * kH, kH, 0);
-    gemm(G, dZlo, kH, 1, W, 1, kH, out, 2 * kH, N, 2 * kH, kH, G_ACCUM);
+    const int nz = (K + kKC - 1) / kKC, tiles = M / (16 * MT) * 2;
+    hipLaunchKernelGGL(k_wgrad<MT>, dim3((nz + 7) / 8 * 8 * tiles), dim3(256), 0, G->s, A, a_ld, M,
+                       dZ, dZlo, K, nz, G->wpart);
+    hipLaunchKernelGGL(k_sum_wgrad, dim3(nb((long)M * kH)), dim3(256), 0, G->s, G->wpart,
+                       (long)M * kH, nz, out);
 }
 
-template <typename TI, typename TO>
-void spmm(dpdlp_gnn *G, bool csr, const TI *in, long in_ld, TO *out, long out_ld, int accum)
+void spmm_bf16(dpdlp_gnn *G, bool csr, const bf16 *in, long in_ld, bf16 *out)
 {
     const ProblemView &P = G->pv;
     const int nseg = csr ? P.m : P.n;
-    hipLaunchKernelGGL((k_spmm<TI, TO>), dim3(nb(nseg, 4)), dim3(256), 0, G->s, csr ? P.rp : P.cp,
-                       csr ? P.ci : P.ri, csr ? G->vf : G->vtf, nseg, in, in_ld, out, out_ld, accum);
+    hipLaunchKernelGGL(k_spmm_bf16, dim3(nb(nseg, 16)), dim3(256), 0, G->s, csr ? P.rp : P.cp,
+                       csr ? P.ci : P.ri, csr ? G->vf : G->vtf, nseg, in, in_ld, out, 2L * kH);
+}
+void spmm_add(dpdlp_gnn *G, bool csr, const float *in, float *out)
+{
+    const ProblemView &P = G->pv;
+    const int nseg = csr ? P.m : P.n;
+    hipLaunchKernelGGL(k_spmm_f32_add, dim3(nb(nseg, 8)), dim3(256), 0, G->s, csr ? P.rp : P.cp,
+                       csr ? P.ci : P.ri, csr ? G->vf : G->vtf, nseg, in, out);
 }
 
 const bf16 *Hc_of(dpdlp_gnn *G, int l, long *ld)
@@ -480,74 +930,77 @@ const bf16 *Hr_of(dpdlp_gnn *G, int l, long *ld)
     return G->Hr_last;
 }
 
-void forward(dpdlp_gnn *G)
+HeadArgs head_args(dpdlp_gnn *G, double *x0, double *y0)
+{
+    HeadArgs a{};
+    a.N[0] = G->pv.n; a.N[1] = G->pv.m;
+    a.H[0] = G->Hc_last; a.H[1] = G->Hr_last;
+    a.w[0] = G->w + G->off_wx; a.w[1] = G->w + G->off_wy;
+    a.ref[0] = G->xref; a.ref[1] = G->yref;
+    a.pred[0] = G->px; a.pred[1] = G->py;
+    a.out[0] = x0; a.out[1] = y0;
+    a.perm[0] = G->pv.perm_col; a.perm[1] = G->pv.perm_row;
+    a.scale[0] = G->pv.dc; a.scale[1] = G->pv.dr;
+    a.tgt[0] = G->tx; a.tgt[1] = G->ty;
+    a.dpred[0] = G->dpx; a.dpred[1] = G->dpy;
+    a.dH[0] = G->dHc; a.dH[1] = G->dHr;
+    a.part[0] = G->lpart; a.part[1] = G->lpart + nb(G->pv.n);
+    return a;
+}
+
+// x0, y0: device vectors for the prediction in the original order and space
+// (null where it is not wanted)
+void forward(dpdlp_gnn *G, double *x0, double *y0)
 {
     const int m = G->pv.m, n = G->pv.n, L = G->L;
-    const int RB = G_RELU | G_OUT_BF16;
-    gemm(G, G->Xc, kF, 1, G->wb + G->off_cin, kH, 1, G->INc[1], 2 * kH, n, kH, kF, RB);
-    gemm(G, G->Xr, kF, 1, G->wb + G->off_rin, kH, 1, G->INr[1], 2 * kH, m, kH, kF, RB);
+    hipLaunchKernelGGL(k_embed, dim3(nb(n, 64) + nb(m, 64)), dim3(256), 0, G->s, n, G->Xc,
+                       G->wf + G->off_cin, G->INc[1], m, G->Xr, G->wf + G->off_rin, G->INr[1]);
     for (int l = 1; l <= L; ++l) {
-        spmm<bf16, bf16>(G, true, G->INc[l], 2 * kH, G->INr[l] + kH, 2 * kH, 0);
+        spmm_bf16(G, true, G->INc[l], 2 * kH, G->INr[l] + kH);
         long ldr;
         bf16 *Hr = (bf16 *)Hr_of(G, l, &ldr);
-        gemm(G, G->INr[l], 2 * kH, 1, G->wb + G->off_r[(size_t)l - 1], kH, 1, Hr, ldr, m, kH, 2 * kH, RB);
-        spmm<bf16, bf16>(G, false, Hr, ldr, G->INc[l] + kH, 2 * kH, 0);
+        dense(G, m, G->INr[l], G->off_r[(size_t)l - 1], Hr, ldr);
+        spmm_bf16(G, false, Hr, ldr, G->INc[l] + kH);
         long ldc;
         bf16 *Hc = (bf16 *)Hc_of(G, l, &ldc);
-        gemm(G, G->INc[l], 2 * kH, 1, G->wb + G->off_c[(size_t)l - 1], kH, 1, Hc, ldc, n, kH, 2 * kH, RB);
+        dense(G, n, G->INc[l], G->off_c[(size_t)l - 1], Hc, ldc);
     }
-    hipLaunchKernelGGL(k_head, dim3(nb(n)), dim3(256), 0, G->s, n, G->Hc_last, (long)kH,
-                       G->w + G->off_wx, G->xref, G->px);
-    hipLaunchKernelGGL(k_head, dim3(nb(m)), dim3(256), 0, G->s, m, G->Hr_last, (long)kH,
-                       G->w + G->off_wy, G->yref, G->py);
+    hipLaunchKernelGGL(k_head, dim3(nb(n) + nb(m)), dim3(256), 0, G->s, head_args(G, x0, y0));
 }
 
 void backward(dpdlp_gnn *G)
 {
     const int m = G->pv.m, n = G->pv.n, L = G->L;
-    const unsigned bn_ = nb(n), bm_ = nb(m);
-    hipLaunchKernelGGL(k_head_bwd, dim3(bn_), dim3(256), 0, G->s, n, G->px, G->tx, G->w + G->off_wx,
-                       G->dpx, G->dHc, G->lpart);
-    hipLaunchKernelGGL(k_head_bwd, dim3(bm_), dim3(256), 0, G->s, m, G->py, G->ty, G->w + G->off_wy,
-                       G->dpy, G->dHr, G->lpart + bn_);
-    hipLaunchKernelGGL(k_sum_double, dim3(1), dim3(256), 0, G->s, G->lpart, (int)bn_, G->lsum);
-    hipLaunchKernelGGL(k_sum_double, dim3(1), dim3(256), 0, G->s, G->lpart + bn_, (int)bm_, G->lsum + 1);
-    const int ch = 1024;
-    const int ncx = (n + ch - 1) / ch, ncy = (m + ch - 1) / ch;
-    hipLaunchKernelGGL(k_head_wgrad, dim3(ncx), dim3(kH), 0, G->s, n, ch, G->Hc_last, (long)kH, G->dpx, G->wpart);
-    hipLaunchKernelGGL(k_sum_chunks, dim3(1), dim3(kH), 0, G->s, G->wpart, (long)kH, ncx, G->g + G->off_wx, (long)kH, 0);
-    hipLaunchKernelGGL(k_head_wgrad, dim3(ncy), dim3(kH), 0, G->s, m, ch, G->Hr_last, (long)kH, G->dpy, G->wpart);
-    hipLaunchKernelGGL(k_sum_chunks, dim3(1), dim3(kH), 0, G->s, G->wpart, (long)kH, ncy, G->g + G->off_wy, (long)kH, 0);
+    const HeadArgs ha = head_args(G, nullptr, nullptr);
+    hipLaunchKernelGGL(k_head_bwd, dim3(nb(n) + nb(m)), dim3(256), 0, G->s, ha);
+    hipLaunchKernelGGL(k_sum_double, dim3(2), dim3(256), 0, G->s, G->lpart, (int)nb(n), (int)nb(m), G->lsum);
+    const int ncx = (int)nb(n, kHeadChunk), ncy = (int)nb(m, kHeadChunk);
+    hipLaunchKernelGGL(k_head_wgrad, dim3(ncx + ncy), dim3(64), 0, G->s, ha, G->wpart);
+    hipLaunchKernelGGL(k_sum_head, dim3(2), dim3(kH), 0, G->s, G->wpart, ncx, ncy, G->g + G->off_wx,
+                       G->g + G->off_wy);
 
     for (int l = L; l >= 1; --l) {
         long ldc, ldr;
         const bf16 *Hc = Hc_of(G, l, &ldc);
         const bf16 *Hr = Hr_of(G, l, &ldr);
-        // column update of layer l
-        hipLaunchKernelGGL(k_relu_bwd, dim3(nb((long)n * kH)), dim3(256), 0, G->s, (long)n, G->dHc,
-                           (long)kH, Hc, ldc, G->dZc, G->dZc_lo);
-        wgrad(G, G->INc[l], 2 * kH, 2 * kH, G->dZc, G->dZc_lo, n, G->g + G->off_c[(size_t)l - 1]);
-        dgrad(G, G->dZc, G->dZc_lo, G->wb + G->off_c[(size_t)l - 1], G->dINc, n);
-        spmm<float, float>(G, true, G->dINc + kH, 2 * kH, G->dHr, kH, 1);   // dH_r^l += A~ dS_c
+        const long oc = G->off_c[(size_t)l - 1], orow = G->off_r[(size_t)l - 1];
+        // column update of layer l; dH_c becomes that of layer l - 1 (without
+        // the row update's part, added below)
+        hipLaunchKernelGGL(k_dgrad, dim3(dense_grid(n)), dim3(256), 0, G->s, n, G->dHc, Hc, ldc,
+                           G->wt + oc, G->dZc, G->dZc_lo, G->dSc);
+        wgrad<4>(G, G->INc[l], 2 * kH, 2 * kH, G->dZc, G->dZc_lo, n, G->g + oc);
+        spmm_add(G, true, G->dSc, G->dHr);                          // dH_r^l += A~ dS_c
         // row update of layer l
-        hipLaunchKernelGGL(k_relu_bwd, dim3(nb((long)m * kH)), dim3(256), 0, G->s, (long)m, G->dHr,
-                           (long)kH, Hr, ldr, G->dZr, G->dZr_lo);
-        wgrad(G, G->INr[l], 2 * kH, 2 * kH, G->dZr, G->dZr_lo, m, G->g + G->off_r[(size_t)l - 1]);
-        dgrad(G, G->dZr, G->dZr_lo, G->wb + G->off_r[(size_t)l - 1], G->dINr, m);
-        // gradients of the previous layer's outputs
-        hipLaunchKernelGGL(k_copy_rows, dim3(nb((long)n * kH)), dim3(256), 0, G->s, (long)n, G->dINc,
-                           2L * kH, G->dHc, (long)kH);
-        spmm<float, float>(G, false, G->dINr + kH, 2 * kH, G->dHc, kH, 1);  // dH_c^{l-1} += A~^T dS_r
-        hipLaunchKernelGGL(k_copy_rows, dim3(nb((long)m * kH)), dim3(256), 0, G->s, (long)m, G->dINr,
-                           2L * kH, G->dHr, (long)kH);
+        hipLaunchKernelGGL(k_dgrad, dim3(dense_grid(m)), dim3(256), 0, G->s, m, G->dHr, Hr, ldr,
+                           G->wt + orow, G->dZr, G->dZr_lo, G->dSr);
+        wgrad<4>(G, G->INr[l], 2 * kH, 2 * kH, G->dZr, G->dZr_lo, m, G->g + orow);
+        spmm_add(G, false, G->dSr, G->dHc);                         // dH_c^{l-1} += A~^T dS_r
     }
     // embeddings
-    hipLaunchKernelGGL(k_relu_bwd, dim3(nb((long)n * kH)), dim3(256), 0, G->s, (long)n, G->dHc,
-                       (long)kH, G->INc[1], 2L * kH, G->dZc, G->dZc_lo);
-    wgrad(G, G->Xc, kF, kF, G->dZc, G->dZc_lo, n, G->g + G->off_cin);
-    hipLaunchKernelGGL(k_relu_bwd, dim3(nb((long)m * kH)), dim3(256), 0, G->s, (long)m, G->dHr,
-                       (long)kH, G->INr[1], 2L * kH, G->dZr, G->dZr_lo);
-    wgrad(G, G->Xr, kF, kF, G->dZr, G->dZr_lo, m, G->g + G->off_rin);
+    hipLaunchKernelGGL(k_relu_bwd, dim3(nb(((long)n + m) * 32)), dim3(256), 0, G->s, (long)n, G->dHc,
+                       G->INc[1], G->dZc, G->dZc_lo, (long)m, G->dHr, G->INr[1], G->dZr, G->dZr_lo);
+    wgrad<1>(G, G->Xc, kF, kF, G->dZc, G->dZc_lo, n, G->g + G->off_cin);
+    wgrad<1>(G, G->Xr, kF, kF, G->dZr, G->dZr_lo, m, G->g + G->off_rin);
 }
 
 // host or device double vector -> device (staging through tmp when host)
@@ -594,12 +1047,14 @@ int dpdlp_gnn_create(dpdlp_problem *prob, int32_t layers, void *stream, dpdlp_gn
     RCHK(galloc(G.get(), &G->g, (size_t)off));
     RCHK(galloc(G.get(), &G->m1, (size_t)off));
     RCHK(galloc(G.get(), &G->m2, (size_t)off));
-    RCHK(galloc(G.get(), &G->wb, (size_t)off));
+    RCHK(galloc(G.get(), &G->wf, (size_t)off));
+    RCHK(galloc(G.get(), &G->wt, (size_t)off));
     GCHK(hipMemsetAsync(G->w, 0, sizeof(float) * off, G->s));
     GCHK(hipMemsetAsync(G->g, 0, sizeof(float) * off, G->s));
     GCHK(hipMemsetAsync(G->m1, 0, sizeof(float) * off, G->s));
     GCHK(hipMemsetAsync(G->m2, 0, sizeof(float) * off, G->s));
-    GCHK(hipMemsetAsync(G->wb, 0, sizeof(bf16) * off, G->s));
+    GCHK(hipMemsetAsync(G->wf, 0, sizeof(bf16) * off, G->s));
+    GCHK(hipMemsetAsync(G->wt, 0, sizeof(bf16) * off, G->s));
     RCHK(galloc(G.get(), &G->vf, (size_t)nnz));
     RCHK(galloc(G.get(), &G->vtf, (size_t)nnz));
     if (nnz) {
@@ -622,14 +1077,14 @@ int dpdlp_gnn_create(dpdlp_problem *prob, int32_t layers, void *stream, dpdlp_gn
     RCHK(galloc(G.get(), &G->Hr_last, (size_t)m * kH));
     RCHK(galloc(G.get(), &G->dHc, (size_t)n * kH));
     RCHK(galloc(G.get(), &G->dHr, (size_t)m * kH));
-    RCHK(galloc(G.get(), &G->dINc, (size_t)n * 2 * kH));
-    RCHK(galloc(G.get(), &G->dINr, (size_t)m * 2 * kH));
+    RCHK(galloc(G.get(), &G->dSc, (size_t)n * kH));
+    RCHK(galloc(G.get(), &G->dSr, (size_t)m * kH));
     RCHK(galloc(G.get(), &G->dZc, (size_t)n * kH));
     RCHK(galloc(G.get(), &G->dZr, (size_t)m * kH));
     RCHK(galloc(G.get(), &G->dZc_lo, (size_t)n * kH));
     RCHK(galloc(G.get(), &G->dZr_lo, (size_t)m * kH));
     const long nzmax = (std::max(n, m) + kKC - 1) / kKC;
-    RCHK(galloc(G.get(), &G->wpart, (size_t)std::max<long>(nzmax * 2 * kH * kH, (n / 1024 + 2) * kH)));
+    RCHK(galloc(G.get(), &G->wpart, (size_t)std::max<long>(nzmax * 4 * kH * kH, ((n + m) / kHeadChunk + 2) * kH)));
     RCHK(galloc(G.get(), &G->lpart, (size_t)(nb(n) + nb(m))));
     RCHK(galloc(G.get(), &G->lsum, 2));
     double **dn[] = {&G->ref_c, &G->ref_x, &G->tmp_n, &G->tmp_n2};
@@ -657,7 +1112,7 @@ int dpdlp_gnn_set_params(dpdlp_gnn *G, const float *params, int64_t count, void 
     if (!G || !params || count != G->n_params) { set_error("bad arguments"); return DPDLP_E_INVALID_ARG; }
     G->s = (hipStream_t)stream;
     GCHK(hipMemcpyAsync(G->w, params, sizeof(float) * count, hipMemcpyHostToDevice, G->s));
-    hipLaunchKernelGGL(k_f2bf, dim3(nb(count)), dim3(256), 0, G->s, G->w, G->wb, (long)count);
+    hipLaunchKernelGGL(k_pack, dim3(nb(G->off_wx)), dim3(256), 0, G->s, G->w, G->wf, G->wt, G->off_wx);
     GCHK(hipMemsetAsync(G->m1, 0, sizeof(float) * count, G->s));
     GCHK(hipMemsetAsync(G->m2, 0, sizeof(float) * count, G->s));
     G->adam_t = 0;
@@ -704,10 +1159,9 @@ int dpdlp_gnn_set_instance(dpdlp_gnn *G, const double *c, const double *con_lo, 
     RCHK(to_dev(G, c, mem_kind, G->tmp_n, n, &dc_));
     RCHK(to_dev(G, con_lo, mem_kind, G->tmp_m, m, &dlo));
     RCHK(to_dev(G, con_hi, mem_kind, G->tmp_m2, m, &dhi));
-    hipLaunchKernelGGL(k_feat_col, dim3(nb(n)), dim3(256), 0, G->s, n, G->pv.perm_col, G->pv.dc, dc_,
-                       G->ref_c, G->ref_x, G->pv.vlo0, G->pv.vhi0, G->Xc, G->xref);
-    hipLaunchKernelGGL(k_feat_row, dim3(nb(m)), dim3(256), 0, G->s, m, G->pv.perm_row, G->pv.dr, dlo,
-                       dhi, G->ref_b, G->ref_y, G->Xr, G->yref);
+    FeatArgs f{n, m, G->pv.perm_col, G->pv.perm_row, G->pv.dc, G->pv.dr, dc_, G->ref_c, G->ref_x,
+               G->pv.vlo0, G->pv.vhi0, dlo, dhi, G->ref_b, G->ref_y, G->Xc, G->Xr, G->xref, G->yref};
+    hipLaunchKernelGGL(k_features, dim3(nb(n) + nb(m)), dim3(256), 0, G->s, f);
     GCHK(hipGetLastError());
     GCHK(hipStreamSynchronize(G->s));
     G->have_inst = true;
@@ -721,21 +1175,12 @@ int dpdlp_gnn_forward(dpdlp_gnn *G, double *x0, double *y0, int32_t mem_kind, vo
     if (!G->have_inst) { set_error("dpdlp_gnn_set_instance first"); return DPDLP_E_INVALID_ARG; }
     G->s = (hipStream_t)stream;
     const int m = G->pv.m, n = G->pv.n;
-    forward(G);
-    if (x0) {
-        double *d = mem_kind == DPDLP_MEM_DEVICE ? x0 : G->tmp_n2;
-        hipLaunchKernelGGL(k_unperm_scale, dim3(nb(n)), dim3(256), 0, G->s, n, G->px, G->pv.perm_col,
-                           G->pv.dc, 1, d);
-        if (mem_kind == DPDLP_MEM_HOST)
-            GCHK(hipMemcpyAsync(x0, d, sizeof(double) * n, hipMemcpyDeviceToHost, G->s));
-    }
-    if (y0) {
-        double *d = mem_kind == DPDLP_MEM_DEVICE ? y0 : G->tmp_m3;
-        hipLaunchKernelGGL(k_unperm_scale, dim3(nb(m)), dim3(256), 0, G->s, m, G->py, G->pv.perm_row,
-                           G->pv.dr, 1, d);
-        if (mem_kind == DPDLP_MEM_HOST)
-            GCHK(hipMemcpyAsync(y0, d, sizeof(double) * m, hipMemcpyDeviceToHost, G->s));
-    }
+    const bool host = mem_kind == DPDLP_MEM_HOST;
+    double *dx = x0 ? (host ? G->tmp_n2 : x0) : nullptr;
+    double *dy = y0 ? (host ? G->tmp_m3 : y0) : nullptr;
+    forward(G, dx, dy);
+    if (host && x0) GCHK(hipMemcpyAsync(x0, dx, sizeof(double) * n, hipMemcpyDeviceToHost, G->s));
+    if (host && y0) GCHK(hipMemcpyAsync(y0, dy, sizeof(double) * m, hipMemcpyDeviceToHost, G->s));
     GCHK(hipGetLastError());
     GCHK(hipStreamSynchronize(G->s));
     return DPDLP_OK;
@@ -752,9 +1197,9 @@ int dpdlp_gnn_backward(dpdlp_gnn *G, const double *x_target, const double *y_tar
     const double *dx, *dy;
     RCHK(to_dev(G, x_target, mem_kind, G->tmp_n, n, &dx));
     RCHK(to_dev(G, y_target, mem_kind, G->tmp_m, m, &dy));
-    hipLaunchKernelGGL(k_perm_scale, dim3(nb(n)), dim3(256), 0, G->s, n, dx, G->pv.perm_col, G->pv.dc, 0, G->tx);
-    hipLaunchKernelGGL(k_perm_scale, dim3(nb(m)), dim3(256), 0, G->s, m, dy, G->pv.perm_row, G->pv.dr, 0, G->ty);
-    forward(G);
+    hipLaunchKernelGGL(k_targets, dim3(nb(n) + nb(m)), dim3(256), 0, G->s, n, dx, G->pv.perm_col,
+                       G->pv.dc, G->tx, m, dy, G->pv.perm_row, G->pv.dr, G->ty);
+    forward(G, nullptr, nullptr);
     backward(G);
     double h[2];
     GCHK(hipMemcpyAsync(h, G->lsum, sizeof(h), hipMemcpyDeviceToHost, G->s));
@@ -772,7 +1217,8 @@ int dpdlp_gnn_adam_step(dpdlp_gnn *G, double lr, double beta1, double beta2, dou
     const float c1 = (float)(1.0 - std::pow(beta1, G->adam_t));
     const float c2 = (float)(1.0 - std::pow(beta2, G->adam_t));
     hipLaunchKernelGGL(k_adam, dim3(nb(G->n_params)), dim3(256), 0, G->s, G->n_params, G->w, G->g,
-                       G->m1, G->m2, G->wb, (float)lr, (float)beta1, (float)beta2, (float)eps, c1, c2);
+                       G->m1, G->m2, G->wf, G->wt, G->off_wx, (float)lr, (float)beta1, (float)beta2,
+                       (float)eps, c1, c2);
     GCHK(hipGetLastError());
     return DPDLP_OK;
 }
@@ -781,8 +1227,8 @@ int dpdlp_gnn_gemm_test(const uint16_t *A, long a_rs, long a_cs, const uint16_t 
                         long b_cs, float *C, long ldc, int32_t M, int32_t Nc, int32_t K, void *stream)
 {
     if (!A || !B || !C || M < 1 || Nc < 1 || K < 1) { set_error("bad arguments"); return DPDLP_E_INVALID_ARG; }
-    hipLaunchKernelGGL(k_gemm, dim3(nb(M, 64), nb(Nc, 64), 1), dim3(256), 0, (hipStream_t)stream, A, a_rs,
-                       a_cs, B, b_rs, b_cs, (void *)C, ldc, 0L, M, Nc, K, K, 0);
+    hipLaunchKernelGGL(k_gemm, dim3(nb(M, 64), nb(Nc, 64)), dim3(256), 0, (hipStream_t)stream, A, a_rs,
+                       a_cs, B, b_rs, b_cs, C, ldc, M, Nc, K);
     GCHK(hipGetLastError());
     GCHK(hipStreamSynchronize((hipStream_t)stream));
     return DPDLP_OK;
