@@ -322,121 +322,169 @@ __global__ __launch_bounds__(256, 2) void k_dgrad(int N, float *dH, const bf16 *
     }
 }
 
-// Weight gradient partials A^T dZ over chunks of kKC nodes, for both halves of
-// dZ: part[(2 z + half) M 128 + ...].  A workgroup owns 16 MT features of A and
-// 64 of dZ and walks its chunk in steps of 64 nodes: 4 nodes x 4 features per
-// thread and operand are transposed in registers into fragments in LDS, and
-// the next step's loads are in flight meanwhile.  The tiles of one chunk run
-// on one XCD, whose L2 then serves the chunk's rows to all of them.
-template <int MT>
-__global__ __launch_bounds__(256) void k_wgrad(const bf16 *__restrict__ A, long a_ld, int M,
-                                               const bf16 *__restrict__ dZ,
-                                               const bf16 *__restrict__ dZlo, int K, int nz,
-                                               float *__restrict__ part)
+// Weight gradients out = A^T dZ of both node kinds in one launch (kind 0:
+// columns).
+struct WgradArgs {
+    const bf16 *A[2], *dZ[2], *dZlo[2];
+    int M;                        // features of A
+    int K[2], nz[2];              // nodes and their chunks
+    float *part[2], *out[2];
+};
+
+// The partials over chunks of kKC nodes, for both halves of dZ:
+// part[(2 z + half) M 128 + ...].  A workgroup owns 16 MT features of A and
+// 16 NT of dZ and walks its chunk in steps of 64 nodes: 4 nodes x 4 features
+// per thread and operand are transposed in registers into fragments in LDS,
+// with the loads two steps ahead (a chunk's steps are serial).  The layers'
+// tiles are 128 x 128 on 8 waves: at 64 x 64 on 4 waves every row was read
+// and packed eight times and 150k nodes took 70-80 us, now 64 (bound by the
+// MFMA of the chunks' workgroups, 148 for 256 CUs; the chunk size fixes the
+// order of the sums).  Both node kinds share a launch (36 + 44 us apart); the
+// tiles of one chunk run on one XCD.
+template <int MT, int NT>
+__global__ __launch_bounds__(64 * NT) void k_wgrad(WgradArgs a)
 {
-    constexpr int MW = MT == 4 ? 2 : 1, NW = MT == 4 ? 2 : 1;      // tiles of one wave
-    __shared__ uint2 sD[2][2][4][4][64];
+    constexpr int WM = MT == 8 ? 2 : 1, WN = NT / WM;              // the waves' grid
+    constexpr int MW = MT / WM, NW = NT / WN;                      // tiles of one wave
+    constexpr int FG = 4 * NT;                                     // threads per 4 nodes
+    constexpr int kALd = MT == 8 ? 2 * kH : kF;                    // A's row length
+    static_assert(WN * WM == NT && MT <= NT, "one wave per 16 features of dZ");
+    __shared__ uint2 sD[2][2][4][NT][64];
     __shared__ uint2 sA[2][4][MT][64];
-    const int tiles = M / (16 * MT) * 2;
-    const int tile = (blockIdx.x >> 3) % tiles;
-    const int z = (blockIdx.x >> 3) / tiles * 8 + (blockIdx.x & 7);
-    if (z >= nz) return;
-    const int fb = (tile >> 1) * 16 * MT, jb = (tile & 1) * 64;
-    const int k0 = z * kKC, k1 = min(K, k0 + kKC);
+    constexpr int n_tiles = kH / (16 * NT);
+    const int tiles = a.M / (16 * MT) * n_tiles;
+    const int first = (a.nz[0] + 7) / 8 * 8 * tiles;        // kind 0's workgroups
+    const int kind = (int)blockIdx.x < first ? 0 : 1;
+    const int b = kind ? blockIdx.x - first : blockIdx.x;
+    const int tile = (b >> 3) % tiles;
+    const int z = (b >> 3) / tiles * 8 + (b & 7);
+    if (z >= a.nz[kind]) return;
+    const bf16 *__restrict__ A = a.A[kind], *__restrict__ dZ = a.dZ[kind], *__restrict__ dZlo = a.dZlo[kind];
+    const int fb = tile / n_tiles * 16 * MT, jb = tile % n_tiles * 16 * NT;
+    const int k0 = z * kKC, k1 = min(a.K[kind], k0 + kKC);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int q = tid >> 4, fg = tid & 15;
-    const bool loads_a = MT == 4 || fg < 4 * MT;
-    const int mt0 = MT == 4 ? (wave & 1) * 2 : 0, nt0 = MT == 4 ? (wave >> 1) * 2 : wave;
-    uint2 rd[2][4], ra[4] = {};
-    auto load = [&](int k) {
+    // (16 neighbouring lanes read one 128-byte line of a row)
+    const int q = tid / FG, fg = tid % FG;
+    const bool loads_a = MT == NT || fg < 4 * MT;
+    const int mt0 = (wave % WM) * MW, nt0 = (wave / WM) * NW;
+    struct Regs { uint2 hi[4], lo[4], a[4]; };
+    // A step costs about as many cycles of address and packing instructions as
+    // of MFMA, so in a full chunk a step's 12 loads share three base addresses
+    // and nothing is checked; a chunk with fewer than kKC nodes reads rows past
+    // its end as zeros.
+    const int ca = fb + 4 * (loads_a ? fg : 0);
+    auto load = [&](auto full, int k, Regs &v) {
+        if constexpr (decltype(full)::value) k = min(k, k1 - 64);      // loads ahead of the last steps
+        const long row = k + 4 * q;
+        const bf16 *h = dZ + row * kH + jb + 4 * fg, *l = dZlo + row * kH + jb + 4 * fg;
+        const bf16 *p = A + row * kALd + ca;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int row = k + 4 * q + r;
-            const bool in = row < k1;
-            const long o = (long)(in ? row : k0) * kH + jb + 4 * fg;
-            const uint2 none = make_uint2(0, 0);
-            rd[0][r] = in ? *(const uint2 *)(dZ + o) : none;
-            rd[1][r] = in ? *(const uint2 *)(dZlo + o) : none;
-            if (loads_a) ra[r] = in ? *(const uint2 *)(A + (long)row * a_ld + fb + 4 * fg) : none;
+            if constexpr (!decltype(full)::value) {
+                v.hi[r] = v.lo[r] = v.a[r] = make_uint2(0, 0);
+                if (row + r >= k1) continue;
+            }
+            v.hi[r] = *(const uint2 *)(h + r * kH);
+            v.lo[r] = *(const uint2 *)(l + r * kH);
+            v.a[r] = *(const uint2 *)(p + r * kALd);
         }
     };
     // 4 nodes x 4 features -> the 4 features' fragments, which are neighbours
+    // in tile fg >> 2; tile t's slots are rotated by 16 t, so that a store's 16
+    // lanes meet two to a bank instead of four
+    const int t4 = fg >> 2;
     auto put = [&](uint2 (&t)[64], const uint2 (&v)[4]) {
-        uint4 *o = (uint4 *)&t[(q & 3) * 16 + (fg & 3) * 4];
-        const uint32_t lo = 0xffffu, hi = 0xffff0000u;
-        o[0] = make_uint4((v[0].x & lo) | (v[1].x << 16), (v[2].x & lo) | (v[3].x << 16),
-                          (v[0].x >> 16) | (v[1].x & hi), (v[2].x >> 16) | (v[3].x & hi));
-        o[1] = make_uint4((v[0].y & lo) | (v[1].y << 16), (v[2].y & lo) | (v[3].y << 16),
-                          (v[0].y >> 16) | (v[1].y & hi), (v[2].y >> 16) | (v[3].y & hi));
+        uint4 *o = (uint4 *)&t[((q & 3) * 16 + (fg & 3) * 4 + 16 * t4) & 63];
+        constexpr uint32_t lo = 0x05040100u, hi = 0x07060302u;     // low / high halves of two words
+        auto two = [](uint32_t x, uint32_t y, uint32_t sel) { return __builtin_amdgcn_perm(y, x, sel); };
+        o[0] = make_uint4(two(v[0].x, v[1].x, lo), two(v[2].x, v[3].x, lo), two(v[0].x, v[1].x, hi),
+                          two(v[2].x, v[3].x, hi));
+        o[1] = make_uint4(two(v[0].y, v[1].y, lo), two(v[2].y, v[3].y, lo), two(v[0].y, v[1].y, hi),
+                          two(v[2].y, v[3].y, hi));
     };
     float4v acc[2][NW][MW];
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int b = 0; b < NW; ++b)
+        for (int c = 0; c < NW; ++c)
 #pragma unroll
-            for (int a = 0; a < MW; ++a) acc[h][b][a] = float4v{0.f, 0.f, 0.f, 0.f};
-    load(k0);
-    int buf = 0;
-    for (int k = k0; k < k1; k += 64, buf ^= 1) {
-        put(sD[buf][0][q >> 2][fg >> 2], rd[0]);
-        put(sD[buf][1][q >> 2][fg >> 2], rd[1]);
-        if (loads_a) put(sA[buf][q >> 2][fg >> 2], ra);
-        if (k + 64 < k1) load(k + 64);
-        __syncthreads();      // one barrier per step: the buffers alternate
+            for (int r = 0; r < MW; ++r) acc[h][c][r] = float4v{0.f, 0.f, 0.f, 0.f};
+    // one step: the loaded rows to LDS, the loads of two steps on, the products
+    // (one barrier per step: the two LDS buffers alternate)
+    auto step = [&](auto full, int k, auto buf_, Regs &v) {
+        constexpr int buf = decltype(buf_)::value;
+        put(sD[buf][0][q >> 2][t4], v.hi);
+        put(sD[buf][1][q >> 2][t4], v.lo);
+        if (loads_a) put(sA[buf][q >> 2][t4], v.a);
+        load(full, k + 128, v);
+        __syncthreads();
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
             uint2 fa[MW], fd[2][NW];
 #pragma unroll
-            for (int a = 0; a < MW; ++a) fa[a] = sA[buf][ks][mt0 + a][lane];
+            for (int r = 0; r < MW; ++r) fa[r] = sA[buf][ks][mt0 + r][(lane + 16 * (mt0 + r)) & 63];
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int b = 0; b < NW; ++b) fd[h][b] = sD[buf][h][ks][nt0 + b][lane];
+                for (int c = 0; c < NW; ++c) fd[h][c] = sD[buf][h][ks][nt0 + c][(lane + 16 * (nt0 + c)) & 63];
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int b = 0; b < NW; ++b)
+                for (int c = 0; c < NW; ++c)
 #pragma unroll
-                    for (int a = 0; a < MW; ++a) acc[h][b][a] = mfma(fd[h][b], fa[a], acc[h][b][a]);
+                    for (int r = 0; r < MW; ++r) acc[h][c][r] = mfma(fd[h][c], fa[r], acc[h][c][r]);
         }
-    }
+    };
+    // pairs of steps (a step past the end adds zeros)
+    auto walk = [&](auto full) {
+        Regs v0, v1;
+        load(full, k0, v0);
+        load(full, k0 + 64, v1);
+        for (int k = k0; k < k1; k += 128) {
+            step(full, k, std::integral_constant<int, 0>{}, v0);
+            step(full, k + 64, std::integral_constant<int, 1>{}, v1);
+        }
+    };
+    if (k1 - k0 == kKC) walk(std::true_type{});
+    else walk(std::false_type{});
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int b = 0; b < NW; ++b)
+        for (int c = 0; c < NW; ++c)
 #pragma unroll
-            for (int a = 0; a < MW; ++a) {
-                const float4v c = acc[h][b][a];
-                const long f = fb + (mt0 + a) * 16 + (lane & 15);
-                float *o = part + ((long)(2 * z + h) * M + f) * kH + jb + (nt0 + b) * 16 + 4 * (lane >> 4);
-                *(float4 *)o = make_float4(c[0], c[1], c[2], c[3]);
+            for (int r = 0; r < MW; ++r) {
+                const float4v p = acc[h][c][r];
+                const long f = fb + (mt0 + r) * 16 + (lane & 15);
+                float *o = a.part[kind] + ((long)(2 * z + h) * a.M + f) * kH + jb + (nt0 + c) * 16 + 4 * (lane >> 4);
+                *(float4 *)o = make_float4(p[0], p[1], p[2], p[3]);
             }
 }
 
-// out = (sum of the hi partials in chunk order) + (sum of the lo partials).
-__global__ __launch_bounds__(256) void k_sum_wgrad(const float *__restrict__ part, long stride,
-                                                   int nz, float *__restrict__ out)
+// out = (sum of the hi partials in chunk order) + (sum of the lo partials);
+// blockIdx.y: the node kind.
+__global__ __launch_bounds__(256) void k_sum_wgrad(WgradArgs a)
 {
-    const long e = (long)blockIdx.x * 256 + threadIdx.x;
+    const int kind = blockIdx.y, nz = a.nz[kind];
+    const long stride = (long)a.M * kH, e = (long)blockIdx.x * 256 + threadIdx.x;
     if (e >= stride) return;
+    const float *__restrict__ part = a.part[kind] + e;
     float s = 0.f, t = 0.f;
     int z = 0;
     for (; z + 8 <= nz; z += 8) {
-        float a[8], b[8];
+        float h[8], l[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            a[u] = part[(long)(2 * (z + u)) * stride + e];
-            b[u] = part[(long)(2 * (z + u) + 1) * stride + e];
+            h[u] = part[(long)(2 * (z + u)) * stride];
+            l[u] = part[(long)(2 * (z + u) + 1) * stride];
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) { s += a[u]; t += b[u]; }
+        for (int u = 0; u < 8; ++u) { s += h[u]; t += l[u]; }
     }
     for (; z < nz; ++z) {
-        s += part[(long)(2 * z) * stride + e];
-        t += part[(long)(2 * z + 1) * stride + e];
+        s += part[(long)(2 * z) * stride];
+        t += part[(long)(2 * z + 1) * stride];
     }
-    out[e] = s + t;
+    a.out[kind][e] = s + t;
 }
 
 // ---- the sparse products ---------------------------------------------------------
@@ -890,16 +938,26 @@ void dense(dpdlp_gnn *G, int N, const bf16 *IN, long off, bf16 *out, long ld)
         hipLaunchKernelGGL(k_dense, dim3(dense_grid(N)), dim3(256), 0, G->s, N, IN, G->wf + off, out, ld);
 }
 
-// weight gradient  out[M x 128] = A^T dZ over K nodes (split K, chunk order)
-template <int MT>
-void wgrad(dpdlp_gnn *G, const bf16 *A, long a_ld, int M, const bf16 *dZ, const bf16 *dZlo, int K,
-           float *out)
+// weight gradients of a layer (MT = 8) or of the embeddings (MT = 1)
+template <int MT, int NT>
+void wgrad(dpdlp_gnn *G, const bf16 *Ac, const bf16 *Ar, int M, float *out_c, float *out_r)
 {
-    const int nz = (K + kKC - 1) / kKC, tiles = M / (16 * MT) * 2;
-    hipLaunchKernelGGL(k_wgrad<MT>, dim3((nz + 7) / 8 * 8 * tiles), dim3(256), 0, G->s, A, a_ld, M,
-                       dZ, dZlo, K, nz, G->wpart);
-    hipLaunchKernelGGL(k_sum_wgrad, dim3(nb((long)M * kH)), dim3(256), 0, G->s, G->wpart,
-                       (long)M * kH, nz, out);
+    WgradArgs a{};
+    a.A[0] = Ac; a.A[1] = Ar;
+    a.dZ[0] = G->dZc; a.dZ[1] = G->dZr;
+    a.dZlo[0] = G->dZc_lo; a.dZlo[1] = G->dZr_lo;
+    a.M = M;
+    a.K[0] = G->pv.n; a.K[1] = G->pv.m;
+    int wgs = 0;
+    for (int k = 0; k < 2; ++k) {
+        a.nz[k] = (a.K[k] + kKC - 1) / kKC;
+        wgs += (a.nz[k] + 7) / 8 * 8 * (M / (16 * MT) * (kH / (16 * NT)));
+    }
+    a.part[0] = G->wpart;
+    a.part[1] = G->wpart + (long)a.nz[0] * 2 * M * kH;
+    a.out[0] = out_c; a.out[1] = out_r;
+    hipLaunchKernelGGL((k_wgrad<MT, NT>), dim3(wgs), dim3(64 * NT), 0, G->s, a);
+    hipLaunchKernelGGL(k_sum_wgrad, dim3(nb((long)M * kH), 2), dim3(256), 0, G->s, a);
 }
 
 void spmm_bf16(dpdlp_gnn *G, bool csr, const bf16 *in, long in_ld, bf16 *out)
@@ -988,19 +1046,17 @@ void backward(dpdlp_gnn *G)
         // the row update's part, added below)
         hipLaunchKernelGGL(k_dgrad, dim3(dense_grid(n)), dim3(256), 0, G->s, n, G->dHc, Hc, ldc,
                            G->wt + oc, G->dZc, G->dZc_lo, G->dSc);
-        wgrad<4>(G, G->INc[l], 2 * kH, 2 * kH, G->dZc, G->dZc_lo, n, G->g + oc);
         spmm_add(G, true, G->dSc, G->dHr);                          // dH_r^l += A~ dS_c
         // row update of layer l
         hipLaunchKernelGGL(k_dgrad, dim3(dense_grid(m)), dim3(256), 0, G->s, m, G->dHr, Hr, ldr,
                            G->wt + orow, G->dZr, G->dZr_lo, G->dSr);
-        wgrad<4>(G, G->INr[l], 2 * kH, 2 * kH, G->dZr, G->dZr_lo, m, G->g + orow);
+        wgrad<8, 8>(G, G->INc[l], G->INr[l], 2 * kH, G->g + oc, G->g + orow);
         spmm_add(G, false, G->dSr, G->dHc);                         // dH_c^{l-1} += A~^T dS_r
     }
     // embeddings
     hipLaunchKernelGGL(k_relu_bwd, dim3(nb(((long)n + m) * 32)), dim3(256), 0, G->s, (long)n, G->dHc,
                        G->INc[1], G->dZc, G->dZc_lo, (long)m, G->dHr, G->INr[1], G->dZr, G->dZr_lo);
-    wgrad<1>(G, G->Xc, kF, kF, G->dZc, G->dZc_lo, n, G->g + G->off_cin);
-    wgrad<1>(G, G->Xr, kF, kF, G->dZr, G->dZr_lo, m, G->g + G->off_rin);
+    wgrad<1, 4>(G, G->Xc, G->Xr, kF, G->g + G->off_cin, G->g + G->off_rin);
 }
 
 // host or device double vector -> device (staging through tmp when host)
@@ -1083,8 +1139,8 @@ int dpdlp_gnn_create(dpdlp_problem *prob, int32_t layers, void *stream, dpdlp_gn
     RCHK(galloc(G.get(), &G->dZr, (size_t)m * kH));
     RCHK(galloc(G.get(), &G->dZc_lo, (size_t)n * kH));
     RCHK(galloc(G.get(), &G->dZr_lo, (size_t)m * kH));
-    const long nzmax = (std::max(n, m) + kKC - 1) / kKC;
-    RCHK(galloc(G.get(), &G->wpart, (size_t)std::max<long>(nzmax * 4 * kH * kH, ((n + m) / kHeadChunk + 2) * kH)));
+    const long chunks = (n + kKC - 1) / kKC + (m + kKC - 1) / kKC;
+    RCHK(galloc(G.get(), &G->wpart, (size_t)std::max<long>(chunks * 4 * kH * kH, ((n + m) / kHeadChunk + 2) * kH)));
     RCHK(galloc(G.get(), &G->lpart, (size_t)(nb(n) + nb(m))));
     RCHK(galloc(G.get(), &G->lsum, 2));
     double **dn[] = {&G->ref_c, &G->ref_x, &G->tmp_n, &G->tmp_n2};
