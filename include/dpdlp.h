@@ -300,8 +300,8 @@ int dpdlp_kkt(dpdlp_problem *prob, const double *x, const double *y, double tau,
  * dpdlp_get_scaling and tau = eta / omega the result is the solver's own
  * termination measure at (x, y), the one dpdlp_kkt reports.
  * The call is asynchronous on `stream` and allocates nothing: its partial
- * sums live in a fixed 3.7 MB device array that each GPU holds until the
- * process ends, which bounds m and n to [1, 16777216] (INVALID_ARG beyond).
+ * sums live in a fixed 0.23 MB device array that each GPU holds until the
+ * process ends; m and n lie in [1, 16777216] (INVALID_ARG beyond).
  * Calls that overlap on one GPU share that array and race.  INVALID_ARG for
  * NULL pointers, host memory, sizes out of range or tau <= 0; HIP for a
  * launch failure.                                                        */
