@@ -227,6 +227,37 @@ void build_tiles(const int32_t *ptr, int32_t nseg, int32_t tile_nnz,
     }
 }
 
+void merge_short_splits(std::vector<Tile> &tiles)
+{
+    std::vector<Tile> out;
+    bool merged = false;
+    for (size_t i = 0; i < tiles.size(); ++i) {
+        Tile t = tiles[i];
+        if (t.npieces > 0 && t.npieces <= kMergePieces) {
+            const int np = t.npieces;
+            t.piece = t.nnz_end - t.nnz_begin;
+            t.nnz_end = tiles[i + (size_t)np - 1].nnz_end;
+            t.npieces = -np;
+            i += (size_t)np - 1;
+            merged = true;
+        }
+        out.push_back(t);
+    }
+    tiles.swap(out);
+    if (!merged) return;
+    // the launch maps an eighth of the tiles, in order, to each XCD
+    const size_t per = (tiles.size() + 7) / 8;
+    for (size_t b = 0; b < tiles.size(); b += per) {
+        const size_t e = std::min(b + per, tiles.size());
+        // the pieces of a larger split stay consecutive: a run that starts
+        // inside one keeps its rest in front
+        size_t from = b;
+        while (from < e && tiles[from].npieces > 0 && tiles[from].piece > 0) ++from;
+        std::stable_partition(tiles.begin() + (ptrdiff_t)from, tiles.begin() + (ptrdiff_t)e,
+                              [](const Tile &t) { return t.npieces < 0; });
+    }
+}
+
 void choose_sum_widths(std::vector<Tile> &tiles, const int32_t *ptr)
 {
     // threads only where the tiles hold enough segments to pay for starting
@@ -239,7 +270,7 @@ void choose_sum_widths(std::vector<Tile> &tiles, const int32_t *ptr)
         std::vector<int32_t> longest((size_t)kMaxSegs + 1);
         for (size_t i = nt * (size_t)t / nth; i < nt * (size_t)(t + 1) / nth; ++i) {
             Tile &d = tiles[i];
-            if (d.npieces > 0) continue;
+            if (d.npieces != 0) continue;
             int32_t groups = d.seg_end - d.seg_begin;
             for (int32_t s = 0; s < groups; ++s)
                 longest[(size_t)s] = ptr[d.seg_begin + s + 1] - ptr[d.seg_begin + s];

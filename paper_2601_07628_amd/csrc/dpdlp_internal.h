@@ -69,6 +69,14 @@ void sort_tiles_by_gather(const std::vector<Tile> &tiles, hvec<int32_t> &idx,
 // Slices are S contiguous ranges of the gathered index that hold about
 // nnz / S nonzeros each; gptr[nidx + 1] is the gathered dimension's own
 // pointer array (its nonzero counts as prefix sums).
+// Unsliced tile sets: the pieces of a segment split into at most kMergePieces
+// become one tile (npieces = -pieces, piece = nonzeros per piece) that one
+// workgroup walks, so that no launch has to add them up; such tiles come
+// first in each XCD's contiguous run of tiles, so that none of them starts
+// last.  Larger splits stay consecutive tiles.
+constexpr int kMergePieces = 4;
+void merge_short_splits(std::vector<Tile> &tiles);
+
 // Width of the FP64 segment sums: for every whole tile the 2^w lanes per
 // segment with the least modelled time of the tile's four waves goes into
 // bits 8.. of width_log2 (bits 0-7 keep the width from the mean length).

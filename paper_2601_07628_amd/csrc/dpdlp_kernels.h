@@ -218,7 +218,8 @@ __global__ __launch_bounds__(kBlock) void k_tile(Op op0, const Tile *__restrict_
     op.slice = d.slice;
     seg_ptr += (size_t)d.slice * seg_stride;
     const int nnz0 = d.nnz_begin;
-    const int cnt = d.nnz_end - d.nnz_begin;
+    // (a merged tile of -npieces pieces of d.piece nonzeros starts with its first)
+    const int cnt = d.npieces < 0 ? d.piece : d.nnz_end - d.nnz_begin;
     const int nseg = d.seg_end - d.seg_begin;
     const bool whole = d.npieces == 0;
 
@@ -348,9 +349,10 @@ __global__ __launch_bounds__(kBlock) void k_tile(Op op0, const Tile *__restrict_
         return;
     }
 
-    // Split segment: reduce this piece and publish it; k_split_fix adds the
-    // pieces in piece order after this launch (no in-kernel cross-workgroup
-    // communication, so no L2-wide fences).
+    // Split segment: reduce this piece and publish it; the pieces are added in
+    // piece order after this launch (k_split_fix, or the sliced steps'
+    // k_combine: no in-kernel cross-workgroup communication, so no L2-wide
+    // fences).
     AT pr[NR];
 #pragma unroll
     for (int q = 0; q < NR; ++q) pr[q] = R::template id<AT>();
@@ -359,9 +361,47 @@ __global__ __launch_bounds__(kBlock) void k_tile(Op op0, const Tile *__restrict_
         for (int q = 0; q < NR; ++q) pr[q] = R::comb(pr[q], s_prod[q][e]);
     }
     block_reduce<R, NR>(pr, s_redp);
-    if (threadIdx.x == 0) {
+    if (d.npieces > 0) {
+        if (threadIdx.x == 0) {
 #pragma unroll
-        for (int q = 0; q < NR; ++q) carries[(size_t)q * ntiles + t] = pr[q];
+            for (int q = 0; q < NR; ++q) carries[(size_t)q * ntiles + t] = pr[q];
+        }
+        return;
+    }
+    // A segment of few pieces stays in this workgroup, which takes them one
+    // after another (the sums are those of the separate pieces).
+    AT tot[NR];
+#pragma unroll
+    for (int q = 0; q < NR; ++q) tot[q] = R::comb(R::template id<AT>(), pr[q]);
+    for (int pb = nnz0 + cnt; pb < d.nnz_end; pb += d.piece) {
+        const int pc = min(d.piece, d.nnz_end - pb);
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int e = min((int)threadIdx.x + q * kBlock, pc - 1);
+            jj[q] = nt_load<NT>(idx + pb + e);
+            aa[q] = nt_load<NT>(val + pb + e);
+        }
+        AT pv[PER][NR];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) op.value(aa[q], jj[q], pv[q]);
+#pragma unroll
+        for (int z = 0; z < NR; ++z) {
+            pr[z] = R::template id<AT>();
+#pragma unroll
+            for (int q = 0; q < PER; ++q)
+                if ((int)threadIdx.x + q * kBlock < pc) pr[z] = R::comb(pr[z], pv[q][z]);
+        }
+        __syncthreads();              // s_redp is still being read
+        block_reduce<R, NR>(pr, s_redp);
+#pragma unroll
+        for (int z = 0; z < NR; ++z) tot[z] = R::comb(tot[z], pr[z]);
+    }
+    if (threadIdx.x == 0) {
+        typename Op::Pre p1;
+        op.template prefetch<NT>(d.seg_begin, p1);
+        op.template epilogue<NT>(d.seg_begin, tot, p1, acc);
+        if (Op::NQ > 0)
+            for (int q = 0; q < Op::NQ; ++q) op.partials[(size_t)q * ntiles + t] = acc[q];
     }
 }
 
@@ -369,6 +409,22 @@ __global__ __launch_bounds__(kBlock) void k_tile(Op op0, const Tile *__restrict_
 struct SplitSeg {
     int32_t seg, t0, npieces, slice;
 };
+// The sum of its pieces in piece order, eight loads at a time.
+template <class R, typename AT>
+__device__ __forceinline__ AT split_sum(const AT *carries, int npieces)
+{
+    AT r = R::template id<AT>();
+    int pc = 0;
+    for (; pc + 8 <= npieces; pc += 8) {
+        AT v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = carries[pc + u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) r = R::comb(r, v[u]);
+    }
+    for (; pc < npieces; ++pc) r = R::comb(r, carries[pc]);
+    return r;
+}
 
 // Finish split segments: one thread per split segment sums its pieces'
 // carries in piece order and runs the epilogue; the segment's partial-sum
@@ -391,11 +447,8 @@ __global__ __launch_bounds__(64) void k_split_fix(Op op0, const SplitSeg *__rest
     op.resolve();
     AT r[NR];
 #pragma unroll
-    for (int q = 0; q < NR; ++q) {
-        r[q] = R::template id<AT>();
-        for (int pc = 0; pc < sg.npieces; ++pc)
-            r[q] = R::comb(r[q], carries[(size_t)q * ntiles + sg.t0 + pc]);
-    }
+    for (int q = 0; q < NR; ++q)
+        r[q] = split_sum<R>(carries + (size_t)q * ntiles + sg.t0, sg.npieces);
     double acc[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
@@ -605,12 +658,18 @@ struct PartialOp2 {
 // that have slice s, counted with wave ballots over the mask bits.  With
 // Op::NR = 2 the second right-hand side's partials start G entries later.
 // Ops with NQ > 0 (check passes) leave per-block partial sums in
-// op.partials[q * gridDim.x + block].
+// op.partials[q * gridDim.x + block].  A block first completes the partials
+// of its own split segments from their pieces (splits[first[block] ..
+// first[block + 1]), few and in few blocks): as a launch of its own between
+// the tiles and the combine that took 5 us per step.
 template <class Op, bool NT>
 __global__ __launch_bounds__(kBlock) void k_combine(Op op0, int nseg, int S,
-                                                    const typename Op::AT *__restrict__ partial,
+                                                    typename Op::AT *partial,
                                                     const uint8_t *__restrict__ mask,
-                                                    const int *__restrict__ cbase, int64_t G)
+                                                    const int *__restrict__ cbase, int64_t G,
+                                                    const SplitSeg *__restrict__ splits,
+                                                    const int *__restrict__ first, int ntiles,
+                                                    const typename Op::AT *__restrict__ carries)
 {
     using AT = typename Op::AT;
     constexpr int NR = Op::NR;
@@ -625,6 +684,16 @@ __global__ __launch_bounds__(kBlock) void k_combine(Op op0, int nseg, int S,
     op.resolve();
     typename Op::Pre p;
     if (in) op.template prefetch<NT>(j, p);
+    if (splits) {
+        // (stored before the first barrier below, read after it)
+        for (int i = first[blockIdx.x] + threadIdx.x; i < first[blockIdx.x + 1]; i += kBlock) {
+            const SplitSeg sg = splits[i];
+#pragma unroll
+            for (int z = 0; z < NR; ++z)
+                partial[(size_t)z * G + sg.seg] =
+                    split_sum<SumOp>(carries + (size_t)z * ntiles + sg.t0, sg.npieces);
+        }
+    }
     AT r[NR];
 #pragma unroll
     for (int z = 0; z < NR; ++z) r[z] = SumOp::template id<AT>();

@@ -325,6 +325,7 @@ struct TileSet {
     int n = 0;
     SplitSeg *splits = nullptr;     // segments split over several tiles
     int nsplit = 0;
+    int *split_first = nullptr;     // sliced sets: each combine block's range of splits
     int *blk2tile = nullptr;        // sliced sets: workgroup -> tile (-1: idle)
     int grid = 0;                   // sliced sets: launch size
     int seg_stride = 0;             // per-slice pointer stride (0 for the compact sliced form)
@@ -477,11 +478,13 @@ static bool streams_fit_cache(const dpdlp_problem *P)
 
 template <class Op>
 static void launch_combine(dpdlp_problem *P, const Op &op, int nseg, const SlicedSet &ss,
-                           const typename Op::AT *partial)
+                           typename Op::AT *partial)
 {
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(nblk(nseg)), dim3(kBlock), 0, P->s, op, nseg, ss.S, partial,
-                           ss.mask, ss.cbase, ss.G);
+                           ss.mask, ss.cbase, ss.G, (const SplitSeg *)ss.ts.splits,
+                           (const int *)ss.ts.split_first, ss.ts.n,
+                           (const typename Op::AT *)P->carries);
     };
     if (streams_fit_cache(P)) go(k_combine<Op, false>);
     else go(k_combine<Op, true>);
@@ -494,8 +497,13 @@ static void launch_tiles(dpdlp_problem *P, const Op &op, const TileSet &ts, cons
     if (ts.n == 0) return;
     const int remap = P->prm.xcd_remap ? 1 : 0;
     const int grid = ts.blk2tile ? ts.grid : (remap ? ((ts.n + 7) / 8) * 8 : ts.n);
+    // 8 KB of unused LDS keep the largest tiles at 5 workgroups per CU: with 6
+    // or 7 their gathers displace each other's lines (64 iterations of a
+    // 10M-nonzero skewed LP 10.86 ms, at 5 10.41; of a 40M-nonzero one 39.0,
+    // at 6 38.5, at 5 38.7)
+    const unsigned lds = P->prm.tile_nnz > 4 * kBlock ? 8192 : 0;
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), 0, P->s, op, ts.d, ts.n, ts.blk2tile,
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), lds, P->s, op, ts.d, ts.n, ts.blk2tile,
                            ts.seg_stride, seg_ptr, idx, val, (const uint16_t *)ts.pos,
                            (typename Op::AT *)P->carries, remap);
     };
@@ -510,7 +518,7 @@ static void launch_tiles(dpdlp_problem *P, const Op &op, const TileSet &ts, cons
     };
     if (streams_fit_cache(P)) pick(std::false_type{});
     else pick(std::true_type{});
-    if (ts.nsplit)
+    if (ts.nsplit && !ts.split_first)        // (sliced sets: the combine completes them)
         hipLaunchKernelGGL(k_split_fix<Op>, dim3((ts.nsplit + 63) / 64), dim3(64), 0, P->s, op,
                            ts.splits, ts.nsplit, ts.n, (const typename Op::AT *)P->carries);
 }
@@ -573,7 +581,7 @@ static void run_primal(dpdlp_problem *P, const Op &op, const T *y, const T *vt)
         po.v = y; po.partial = (T *)P->part_slices; po.partials = nullptr;
         launch_tiles(P, po, P->sc.ts, P->sc.ptr, P->sc.idx,
                      (const T *)(sizeof(T) == 8 ? (const void *)P->sc.val : (const void *)P->sc.val32));
-        launch_combine(P, op, P->n, P->sc, (const T *)P->part_slices);
+        launch_combine(P, op, P->n, P->sc, (T *)P->part_slices);
         return;
     }
     launch_tiles(P, op, P->tc, P->cp, P->ri, vt);
@@ -625,7 +633,7 @@ static void launch_dual(dpdlp_problem *P, const T *xbar, const T *lo, const T *h
         po.v = xbar; po.partial = (T *)P->part_slices; po.partials = nullptr;
         launch_tiles(P, po, P->sr.ts, P->sr.ptr, P->sr.idx,
                      (const T *)(sizeof(T) == 8 ? (const void *)P->sr.val : (const void *)P->sr.val32));
-        launch_combine(P, op, P->m, P->sr, (const T *)P->part_slices);
+        launch_combine(P, op, P->m, P->sr, (T *)P->part_slices);
         return;
     }
     launch_tiles(P, op, P->tr, P->rp, P->ci, v);
@@ -705,7 +713,7 @@ static int launch_product(dpdlp_problem *P, bool transpose, const Op &op, const 
         PartialOp<double> po;
         po.v = in; po.partial = (double *)P->part_slices; po.partials = nullptr;
         launch_tiles(P, po, ss.ts, ss.ptr, ss.idx, ss.val);
-        launch_combine(P, op, nseg, ss, (const double *)P->part_slices);
+        launch_combine(P, op, nseg, ss, (double *)P->part_slices);
         return (int)nblk(nseg);
     }
     if (transpose) launch_tiles(P, op, P->tc, P->cp, P->ri, P->vt);
@@ -732,7 +740,7 @@ static void launch_checks(dpdlp_problem *P, const double *xh, const double *dx, 
             po.v = xh; po.v2 = dx; po.partial = (double *)P->part_slices; po.G = P->sr.G;
             po.partials = nullptr;
             launch_tiles(P, po, P->sr.ts, P->sr.ptr, P->sr.idx, P->sr.val);
-            launch_combine(P, op, P->m, P->sr, (const double *)P->part_slices);
+            launch_combine(P, op, P->m, P->sr, (double *)P->part_slices);
             P->chk_nr = nblk(P->m);
         } else {
             launch_tiles(P, op, P->tr, P->rp, P->ci, P->v);
@@ -749,7 +757,7 @@ static void launch_checks(dpdlp_problem *P, const double *xh, const double *dx, 
             PartialOp<double> po;
             po.v = yh; po.partial = (double *)P->part_slices; po.partials = nullptr;
             launch_tiles(P, po, P->sc.ts, P->sc.ptr, P->sc.idx, P->sc.val);
-            launch_combine(P, op, P->n, P->sc, (const double *)P->part_slices);
+            launch_combine(P, op, P->n, P->sc, (double *)P->part_slices);
             P->chk_nc = nblk(P->n);
         } else {
             launch_tiles(P, op, P->tc, P->cp, P->ri, P->vt);
@@ -786,6 +794,7 @@ static int build_tileset(dpdlp_problem *P, const hvec<int32_t> &ptr, int32_t nse
                          TileSet &ts, std::vector<Tile> &host_tiles)
 {
     build_tiles(ptr.data(), nseg, P->prm.tile_nnz, host_tiles);
+    merge_short_splits(host_tiles);
     ts.n = (int)host_tiles.size();
     std::vector<SplitSeg> sp;
     for (int i = 0; i < ts.n; ++i) {
@@ -862,9 +871,30 @@ static int build_sliced(dpdlp_problem *P, const hvec<int32_t> &ptr,
     CHK(upload(P, ts.d, sh.tiles.data(), sh.tiles.size() * sizeof(Tile)));
     CHK(dalloc(P, &ts.blk2tile, b2t.size()));
     CHK(upload(P, ts.blk2tile, b2t.data(), b2t.size() * sizeof(int)));
+    std::vector<int> first;
     if (ts.nsplit) {
+        // in the order of the combine's blocks: the original segment of a
+        // compact one is found through the blocks' bases
+        const int nb = (int)nblk(nseg);
+        auto block_of = [&](const SplitSeg &g) {
+            int lo = 0, hi = nb - 1;          // last block whose base is <= g.seg
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) / 2;
+                if (sh.cbase[(size_t)mid * S + g.slice] <= g.seg) lo = mid;
+                else hi = mid - 1;
+            }
+            return lo;
+        };
+        std::vector<std::pair<int, SplitSeg>> by;
+        for (const SplitSeg &g : sp) by.push_back({block_of(g), g});
+        std::stable_sort(by.begin(), by.end(), [](const auto &x, const auto &y) { return x.first < y.first; });
+        first.assign((size_t)nb + 1, 0);
+        for (size_t i = 0; i < by.size(); ++i) { sp[i] = by[i].second; first[(size_t)by[i].first + 1]++; }
+        for (int b = 0; b < nb; ++b) first[(size_t)b + 1] += first[(size_t)b];
         CHK(dalloc(P, &ts.splits, sp.size()));
         CHK(upload(P, ts.splits, sp.data(), sp.size() * sizeof(SplitSeg)));
+        CHK(dalloc(P, &ts.split_first, first.size()));
+        CHK(upload(P, ts.split_first, first.data(), first.size() * sizeof(int)));
     }
     HIPCHK(hipStreamSynchronize(P->s));
     return DPDLP_OK;

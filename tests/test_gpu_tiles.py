@@ -56,3 +56,25 @@ def test_long_segments_among_short_ones(D, O, long_len):  # noqa: F811
     lp = lpgen.LP(m, n, rp, cols.astype(np.int32), val, rng.standard_normal(n), ax - 0.1,
                   np.full(m, np.inf), np.zeros(n), np.full(n, 2.0), name=f"long{long_len}")
     fixed_run(D, O, lp, 130, gpu_kw=dict(tile_nnz=2048))
+
+
+@pytest.mark.parametrize("slices", [0, 8])
+@pytest.mark.parametrize("pieces", [1, 2, 4, 5, 12])
+def test_split_segments_merged_and_not(D, O, pieces, slices):  # noqa: F811
+    """Rows of `pieces` tiles among short ones: up to four pieces stay in one
+    workgroup, more are added up by a launch of their own (unsliced) or by the
+    combine (sliced); with rows of both kinds in one matrix."""
+    rng = np.random.default_rng(10 * pieces + slices)
+    m, n, tile = 900, 4000, 256
+    deg = rng.integers(1, 6, size=m)
+    deg[rng.choice(m, size=7, replace=False)] = pieces * tile - 3
+    deg[rng.choice(m, size=2, replace=False)] = 3 * tile + 1
+    deg[rng.choice(m, size=2, replace=False)] = 9 * tile
+    cols = np.concatenate([np.sort(rng.choice(n, size=d, replace=False)) for d in deg])
+    rp = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    val = rng.standard_normal(cols.size)
+    x = rng.uniform(0, 1, n)
+    ax = np.bincount(np.repeat(np.arange(m), deg), weights=val * x[cols], minlength=m)
+    lp = lpgen.LP(m, n, rp, cols.astype(np.int32), val, rng.standard_normal(n), ax - 0.1,
+                  np.full(m, np.inf), np.zeros(n), np.full(n, 2.0), name=f"pieces{pieces}")
+    fixed_run(D, O, lp, 130, gpu_kw=dict(tile_nnz=tile, gather_slices=slices))
