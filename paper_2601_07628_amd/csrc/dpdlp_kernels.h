@@ -68,14 +68,13 @@ struct MaxOp {
 };
 
 // Tile index of this workgroup.  Workgroups are dispatched round-robin over
-// the 8 XCDs (workgroup b runs on XCD b % 8); with remap on, XCD x processes a
-// contiguous run of tiles so neighbouring segments share that XCD's L2.
-__device__ __forceinline__ int tile_of_block(int remap)
+// the 8 XCDs (workgroup b runs on XCD b % 8); with per_xcd > 0, XCD x processes
+// that many consecutive tiles, so neighbouring segments share that XCD's L2
+// (the grid is then 8 per_xcd).
+__device__ __forceinline__ int tile_of_block(int per_xcd)
 {
     const int b = blockIdx.x;
-    if (!remap) return b;
-    const int per = gridDim.x >> 3;     // grid is a multiple of 8 when remapped
-    return (b & 7) * per + (b >> 3);
+    return per_xcd ? (b & 7) * per_xcd + (b >> 3) : b;
 }
 
 // Lane permutations inside the vector ALU, on 32- or 64-bit values: lane i
@@ -190,15 +189,13 @@ __device__ __forceinline__ void nt_store(T *p, T v)
 constexpr int kPre = 2;                         // prefetched segments per thread
 
 template <class Op, int PER, bool NT>
-__global__ __launch_bounds__(kBlock) void k_tile(Op op0, const Tile *__restrict__ tiles,
-                                                 int ntiles, const int *__restrict__ blk2tile,
-                                                 int seg_stride,
-                                                 const int *__restrict__ seg_ptr,
-                                                 const int *__restrict__ idx,
+__global__ __launch_bounds__(kBlock) void k_tile(const Tile *__restrict__ tiles,
+                                                 const int *__restrict__ blk2tile, int ntiles,
+                                                 int per_xcd, const int *__restrict__ idx,
                                                  const typename Op::MT *__restrict__ val,
+                                                 const int *__restrict__ seg_ptr, int seg_stride,
                                                  const uint16_t *__restrict__ pos,
-                                                 typename Op::AT *__restrict__ carries,
-                                                 int remap)
+                                                 typename Op::AT *__restrict__ carries, Op op0)
 {
     using AT = typename Op::AT;
     using MT = typename Op::MT;
@@ -210,11 +207,10 @@ __global__ __launch_bounds__(kBlock) void k_tile(Op op0, const Tile *__restrict_
     __shared__ double s_red[NQ][kBlock / 64];
     __shared__ AT s_redp[NR][kBlock / 64];
 
-    Op op = op0;
-    op.resolve();             // graph replays: its scalar loads go out with the tile's
-    const int t = blk2tile ? blk2tile[blockIdx.x] : tile_of_block(remap);
+    const int t = blk2tile ? blk2tile[blockIdx.x] : tile_of_block(per_xcd);
     if (t < 0 || t >= ntiles) return;
     const Tile d = tiles[t];
+    Op op = op0;
     op.slice = d.slice;
     seg_ptr += (size_t)d.slice * seg_stride;
     const int nnz0 = d.nnz_begin;
@@ -268,6 +264,10 @@ __global__ __launch_bounds__(kBlock) void k_tile(Op op0, const Tile *__restrict_
         }
         if ((int)threadIdx.x <= nseg) s_ptr[threadIdx.x] = sp0 - nnz0;
     }
+    // graph replays: the run's scalars, whose load and divisions overlap the
+    // loads above (in front of the tile's descriptor they held every kernel
+    // up by a memory round trip)
+    op.resolve();
     // 1c. gathers (all issued before the first product is stored), products to LDS
     if (cnt > 0) {
         AT pv[PER][NR];
@@ -663,13 +663,13 @@ struct PartialOp2 {
 // first[block + 1]), few and in few blocks): as a launch of its own between
 // the tiles and the combine that took 5 us per step.
 template <class Op, bool NT>
-__global__ __launch_bounds__(kBlock) void k_combine(Op op0, int nseg, int S,
-                                                    typename Op::AT *partial,
-                                                    const uint8_t *__restrict__ mask,
-                                                    const int *__restrict__ cbase, int64_t G,
-                                                    const SplitSeg *__restrict__ splits,
+__global__ __launch_bounds__(kBlock) void k_combine(const uint8_t *__restrict__ mask,
+                                                    const int *__restrict__ cbase,
+                                                    typename Op::AT *partial, int nseg, int S,
+                                                    int64_t G, const SplitSeg *__restrict__ splits,
                                                     const int *__restrict__ first, int ntiles,
-                                                    const typename Op::AT *__restrict__ carries)
+                                                    const typename Op::AT *__restrict__ carries,
+                                                    Op op0)
 {
     using AT = typename Op::AT;
     constexpr int NR = Op::NR;
@@ -681,7 +681,6 @@ __global__ __launch_bounds__(kBlock) void k_combine(Op op0, int nseg, int S,
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     Op op = op0;
-    op.resolve();
     typename Op::Pre p;
     if (in) op.template prefetch<NT>(j, p);
     if (splits) {
@@ -732,6 +731,7 @@ __global__ __launch_bounds__(kBlock) void k_combine(Op op0, int nseg, int S,
     double acc[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
+    op.resolve();
     if (in) op.template epilogue<NT>(j, r, p, acc);
     if (Op::NQ > 0) {
         block_reduce<SumOp, NQ>(acc, s_red);

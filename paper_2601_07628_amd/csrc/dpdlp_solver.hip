@@ -481,10 +481,10 @@ static void launch_combine(dpdlp_problem *P, const Op &op, int nseg, const Slice
                            typename Op::AT *partial)
 {
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(nblk(nseg)), dim3(kBlock), 0, P->s, op, nseg, ss.S, partial,
-                           ss.mask, ss.cbase, ss.G, (const SplitSeg *)ss.ts.splits,
+        hipLaunchKernelGGL(kernel, dim3(nblk(nseg)), dim3(kBlock), 0, P->s, ss.mask, ss.cbase,
+                           partial, nseg, ss.S, ss.G, (const SplitSeg *)ss.ts.splits,
                            (const int *)ss.ts.split_first, ss.ts.n,
-                           (const typename Op::AT *)P->carries);
+                           (const typename Op::AT *)P->carries, op);
     };
     if (streams_fit_cache(P)) go(k_combine<Op, false>);
     else go(k_combine<Op, true>);
@@ -496,16 +496,17 @@ static void launch_tiles(dpdlp_problem *P, const Op &op, const TileSet &ts, cons
 {
     if (ts.n == 0) return;
     const int remap = P->prm.xcd_remap ? 1 : 0;
-    const int grid = ts.blk2tile ? ts.grid : (remap ? ((ts.n + 7) / 8) * 8 : ts.n);
+    const int per_xcd = remap ? (ts.n + 7) / 8 : 0;
+    const int grid = ts.blk2tile ? ts.grid : (remap ? 8 * per_xcd : ts.n);
     // 8 KB of unused LDS keep the largest tiles at 5 workgroups per CU: with 6
     // or 7 their gathers displace each other's lines (64 iterations of a
     // 10M-nonzero skewed LP 10.86 ms, at 5 10.41; of a 40M-nonzero one 39.0,
     // at 6 38.5, at 5 38.7)
     const unsigned lds = P->prm.tile_nnz > 4 * kBlock ? 8192 : 0;
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), lds, P->s, op, ts.d, ts.n, ts.blk2tile,
-                           ts.seg_stride, seg_ptr, idx, val, (const uint16_t *)ts.pos,
-                           (typename Op::AT *)P->carries, remap);
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), lds, P->s, ts.d, ts.blk2tile, ts.n,
+                           per_xcd, idx, val, seg_ptr, ts.seg_stride, (const uint16_t *)ts.pos,
+                           (typename Op::AT *)P->carries, op);
     };
     // nonzeros per thread: as many as the largest tile needs
     const int per = (P->prm.tile_nnz + kBlock - 1) / kBlock;
