@@ -194,32 +194,49 @@ __global__ __launch_bounds__(kBlock) void k_lanczos_norm(const double *partials,
     }
 }
 
+// Control block: FP64 scalars kept on the device.
+struct Control {
+    double omega, r0, r_prev, pid_int, pid_prev;
+    double r_primal, r_dual, r_gap, obj_p, obj_d, r;
+    double sums[2 * kNQ];
+    int32_t pid_started, restarts, restart, converged, numerical, n_checks;
+};
+
 // Start point (original space -> scaled, permuted): x = clamp(x0/D_c, X),
-// y = proj_Y(y0/D_r); the anchor is the same point.
-template <typename T>
-__global__ void k_init_x(int n, const double *x0, const int *perm, const double *dc,
-                         const double *vlo, const double *vhi, T *x, T *xa)
+// y = proj_Y(y0/D_r); the anchor and T(z) start as the same point.  FP32 copies
+// where x32 is given; block 0 also writes the control block.
+struct InitArgs {
+    int n, m;
+    const double *x0, *dc, *vlo, *vhi, *y0, *dr, *clo, *chi;
+    const int *pc, *pr;
+    double *x, *xa, *xh, *y, *ya, *yh;
+    float *x32, *xa32, *y32, *ya32;
+    Control *ctl;
+    double omega;
+};
+__global__ __launch_bounds__(kBlock) void k_init(InitArgs a)
 {
-    int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
-    double v = x0 ? x0[perm[j]] / dc[j] : 0.0;
-    v = clampv(v, vlo[j], vhi[j]);
-    x[j] = (T)v;
-    xa[j] = (T)v;
-}
-template <typename T>
-__global__ void k_init_y(int m, const double *y0, const int *perm, const double *dr,
-                         const double *clo, const double *chi, T *y, T *ya)
-{
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= m) return;
-    double v = y0 ? y0[perm[i]] / dr[i] : 0.0;
-    const bool lf = isfinite(clo[i]), hf = isfinite(chi[i]);
-    if (!lf && !hf) v = 0.0;
-    else if (!lf) v = fmin(v, 0.0);
-    else if (!hf) v = fmax(v, 0.0);
-    y[i] = (T)v;
-    ya[i] = (T)v;
+    const int i = blockIdx.x * kBlock + threadIdx.x;
+    if (i == 0) {
+        Control C{};
+        C.omega = a.omega;
+        *a.ctl = C;
+    }
+    if (i < a.n) {
+        double v = a.x0 ? a.x0[a.pc[i]] / a.dc[i] : 0.0;
+        v = clampv(v, a.vlo[i], a.vhi[i]);
+        a.x[i] = v; a.xa[i] = v; a.xh[i] = v;
+        if (a.x32) { a.x32[i] = (float)v; a.xa32[i] = (float)v; }
+    }
+    if (i < a.m) {
+        double v = a.y0 ? a.y0[a.pr[i]] / a.dr[i] : 0.0;
+        const bool lf = isfinite(a.clo[i]), hf = isfinite(a.chi[i]);
+        if (!lf && !hf) v = 0.0;
+        else if (!lf) v = fmin(v, 0.0);
+        else if (!hf) v = fmax(v, 0.0);
+        a.y[i] = v; a.ya[i] = v; a.yh[i] = v;
+        if (a.y32) { a.y32[i] = (float)v; a.ya32[i] = (float)v; }
+    }
 }
 
 // out[perm[i]] = scale[i] * in[i]   (scale may be null)
@@ -251,14 +268,6 @@ __global__ void k_restart(int m, int n, const double *xh, const double *yh, T *x
     if (i < m) { y[i] = (T)yh[i]; ya[i] = (T)yh[i]; }
 }
 
-// Control block: FP64 scalars kept on the device.
-struct Control {
-    double omega, r0, r_prev, pid_int, pid_prev;
-    double r_primal, r_dual, r_gap, obj_p, obj_d, r;
-    double sums[2 * kNQ];
-    int32_t pid_started, restarts, restart, converged, numerical, n_checks;
-};
-
 struct CtlArgs {
     int64_t k, t;
     double eta, eps, beta_suf, beta_nec, beta_art, kp, ki, kd, c_norm, b_norm;
@@ -267,15 +276,18 @@ struct CtlArgs {
 };
 
 // KKT (App. B.4), fixed-point residual (App. B.2, D.2.1), restart decision
-// and PID primal-weight update (App. B.3).  One workgroup.
+// and PID primal-weight update (App. B.3).  One workgroup.  The result also
+// goes to the host's copy of the block (pinned memory), so that the host only
+// waits for the stream.  mode 1 (evaluation) leaves the solver's block alone.
 __global__ __launch_bounds__(kBlock) void k_control(const double *pr, int ntr, const double *pc,
-                                                    int ntc, Control *ctl, CtlArgs a)
+                                                    int ntc, Control *ctl, Control *host, CtlArgs a)
 {
     __shared__ double srow[kNQ], scol[kNQ];
     sum_partials<kNQ>(pr, ntr, kNQ, srow);
     sum_partials<kNQ>(pc, ntc, kNQ, scol);
     if (threadIdx.x != 0) return;
-    Control C = *ctl;
+    Control C{};
+    if (a.mode == 0) C = *ctl;
     for (int q = 0; q < kNQ; ++q) { C.sums[q] = srow[q]; C.sums[kNQ + q] = scol[q]; }
     const double pres = srow[0], py = srow[1], dyy = srow[2], dya = srow[3], yanc = srow[4];
     const double dres = scol[0], cx = scol[1], sx = scol[2], dxx = scol[3], xanc = scol[4];
@@ -284,7 +296,7 @@ __global__ __launch_bounds__(kBlock) void k_control(const double *pr, int ntr, c
     const double dobj = py + sx;
     const double rg = fabs(cx - dobj) / (1.0 + fmax(fabs(cx), fabs(dobj)));
     C.r_primal = rp; C.r_dual = rd; C.r_gap = rg; C.obj_p = cx; C.obj_d = dobj;
-    if (a.mode == 1) { *ctl = C; return; }
+    if (a.mode == 1) { *host = C; return; }
     const double w = C.omega;
     const double r2 = (w / a.eta) * dxx + dyy / (a.eta * w) + 2.0 * dya;
     const double r = sqrt(fmax(r2, 0.0));
@@ -315,6 +327,7 @@ __global__ __launch_bounds__(kBlock) void k_control(const double *pr, int ntr, c
     }
     C.n_checks += 1;
     *ctl = C;
+    *host = C;
 }
 
 // ---------------------------------------------------------------------------
@@ -402,8 +415,8 @@ struct dpdlp_problem {
     double *norm_part = nullptr;
     double *sig_hist = nullptr;
     Control *ctl = nullptr;
-    Control *ctl_eval = nullptr;    // scratch block for dpdlp_kkt
-    Control *h_ctl = nullptr;       // pinned
+    Control *h_ctl = nullptr;       // pinned: the host's copy, and [1] for dpdlp_kkt
+    Control *d_ctl = nullptr;       // its device address
     // host-side scalars
     double eta = 0, sigma_max = 0, omega0 = 0, c_norm = 0, b_norm = 0;
     int power_iters = 0;
@@ -420,6 +433,7 @@ struct dpdlp_problem {
     // graph replay of the runs between checks
     IterDev *iterdev = nullptr;
     hipGraphExec_t graph[2] = {nullptr, nullptr};
+    int graph_runs[2] = {0, 0};     // runs that went out eagerly before the capture
     hipStream_t gstream = nullptr;
     // profiling
     bool prof = false;
@@ -670,9 +684,13 @@ __global__ void k_set_iter(IterDev *d, double tau, double sigma, long long k0)
     d->k0 = k0;
 }
 
-// The check_period - 1 iterations between two checks as one HIP graph (one
-// per precision), captured on a private stream on first use and replayed on
-// the solver's stream after k_set_iter has written the run's scalars.
+// The last check_period - 2 iterations before a check as one HIP graph (one per
+// precision), captured on a private stream on first use and replayed on the
+// solver's stream after k_set_iter has written the run's scalars.  The one
+// iteration in front of them is the check of a fresh epoch where there was a
+// restart and an eager launch otherwise, so one graph serves both kinds of
+// run; with check_period - 1 iterations per graph the runs after a restart
+// went out as single launches, 9 us per iteration of a small LP against 7.
 static int run_graph(dpdlp_problem *P, double tau, double sigma, int64_t k0, int L)
 {
     hipGraphExec_t &ge = P->graph[P->in_fp32 ? 1 : 0];
@@ -775,13 +793,6 @@ static CtlArgs ctl_args(dpdlp_problem *P, int mode)
     a.kp = P->prm.kp; a.ki = P->prm.ki; a.kd = P->prm.kd;
     a.c_norm = P->c_norm; a.b_norm = P->b_norm; a.mode = mode;
     return a;
-}
-
-static int read_ctl(dpdlp_problem *P)
-{
-    HIPCHK(hipMemcpyAsync(P->h_ctl, P->ctl, sizeof(Control), hipMemcpyDeviceToHost, P->s));
-    HIPCHK(hipStreamSynchronize(P->s));
-    return DPDLP_OK;
 }
 
 // ---- setup -----------------------------------------------------------------
@@ -990,7 +1001,7 @@ static int check_buffers(dpdlp_problem *P)
                          P->chi0, P->vlo0, P->vhi0, P->c, P->clo, P->chi, P->vlo, P->vhi, P->dr,
                          P->dc, P->fr, P->fc, P->x, P->y, P->xbar, P->xa, P->ya, P->xh, P->yh,
                          P->dx, P->dy, P->tmp_m, P->tmp_n, P->tmp_m2, P->tmp_n2, P->scal,
-                         P->sig_hist, P->ctl, P->ctl_eval, P->iterdev, P->h_ctl};
+                         P->sig_hist, P->ctl, P->iterdev, P->h_ctl, P->d_ctl};
     for (const void *p : req)
         if (!p) { set_error("internal: a device buffer is not allocated"); return DPDLP_E_HIP; }
     if ((P->tr.nsplit && !P->tr.splits) || (P->tc.nsplit && !P->tc.splits)) {
@@ -1218,9 +1229,9 @@ static int create_impl(const dpdlp_csr_lp *lp_in, const dpdlp_params *params, vo
     CHK(dalloc(P, &P->scal, 16));
     CHK(dalloc(P, &P->sig_hist, 2 * ((size_t)std::max(1, P->prm.power_max_iters) + 2)));
     CHK(dalloc(P, &P->ctl, 1));
-    CHK(dalloc(P, &P->ctl_eval, 1));
     CHK(dalloc(P, &P->iterdev, 1));
-    HIPCHK(hipHostMalloc((void **)&P->h_ctl, sizeof(Control), hipHostMallocDefault));
+    HIPCHK(hipHostMalloc((void **)&P->h_ctl, 2 * sizeof(Control), hipHostMallocDefault));
+    HIPCHK(hipHostGetDevicePointer((void **)&P->d_ctl, P->h_ctl, 0));
 
     // A3: rescaling (Ruiz passes, then one Pock-Chambolle pass)
     hipLaunchKernelGGL(k_fill<double>, dim3(nblk(m)), dim3(kBlock), 0, P->s, P->dr, 1.0, (int64_t)m);
@@ -1316,19 +1327,12 @@ static int init_impl(dpdlp_problem *P, const double *x0, const double *y0, int m
             dy0 = P->tmp_m2;
         } else dy0 = y0;
     }
-    hipLaunchKernelGGL(k_init_x<double>, dim3(nblk(n)), dim3(kBlock), 0, P->s, n, dx0, P->perm_col,
-                       P->dc, P->vlo, P->vhi, P->x, P->xa);
-    hipLaunchKernelGGL(k_init_y<double>, dim3(nblk(m)), dim3(kBlock), 0, P->s, m, dy0, P->perm_row,
-                       P->dr, P->clo, P->chi, P->y, P->ya);
-    HIPCHK(hipMemcpyAsync(P->xh, P->x, sizeof(double) * n, hipMemcpyDeviceToDevice, P->s));
-    HIPCHK(hipMemcpyAsync(P->yh, P->y, sizeof(double) * m, hipMemcpyDeviceToDevice, P->s));
     P->in_fp32 = P->prm.precision == DPDLP_FP32_MIXED;
-    if (P->in_fp32) {
-        hipLaunchKernelGGL((k_convert<double, float>), dim3(nblk(n)), dim3(kBlock), 0, P->s, P->x, P->x32, (int64_t)n);
-        hipLaunchKernelGGL((k_convert<double, float>), dim3(nblk(n)), dim3(kBlock), 0, P->s, P->xa, P->xa32, (int64_t)n);
-        hipLaunchKernelGGL((k_convert<double, float>), dim3(nblk(m)), dim3(kBlock), 0, P->s, P->y, P->y32, (int64_t)m);
-        hipLaunchKernelGGL((k_convert<double, float>), dim3(nblk(m)), dim3(kBlock), 0, P->s, P->ya, P->ya32, (int64_t)m);
-    }
+    InitArgs a{n, m, dx0, P->dc, P->vlo, P->vhi, dy0, P->dr, P->clo, P->chi, P->perm_col, P->perm_row,
+               P->x, P->xa, P->xh, P->y, P->ya, P->yh,
+               P->in_fp32 ? P->x32 : nullptr, P->xa32, P->in_fp32 ? P->y32 : nullptr, P->ya32,
+               P->ctl, P->omega0};
+    hipLaunchKernelGGL(k_init, dim3(nblk(std::max(m, n))), dim3(kBlock), 0, P->s, a);
     P->omega = P->omega0;
     P->k = 0; P->t = 0; P->fp32_iters = 0;
     P->status = DPDLP_RUNNING;
@@ -1338,7 +1342,6 @@ static int init_impl(dpdlp_problem *P, const double *x0, const double *y0, int m
     P->solve_seconds = 0;
     P->log.clear();
     reset_ctl_host(P);
-    HIPCHK(hipMemcpyAsync(P->ctl, P->h_ctl, sizeof(Control), hipMemcpyHostToDevice, P->s));
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(P->s));
     P->initialized = true;
@@ -1380,16 +1383,23 @@ static int iterate_impl(dpdlp_problem *P, int64_t n_iters)
         if (P->t >= P->prm.max_iters) { P->status = DPDLP_ITER_LIMIT; break; }
         const double tau = P->eta / P->omega, sigma = P->eta * P->omega;
         const bool is_check = (P->k == 0) || ((P->t + 1) % K == 0);
-        if (!is_check && P->prm.use_graphs && !P->prof && K > 1 && P->t % K == 0) {
-            // a whole run t .. t+K-2 of non-check iterations, none the last of the call
-            const int L = K - 1;
+        if (!is_check && P->prm.use_graphs && !P->prof && K > 2 && P->t % K == 1) {
+            // the run t .. t+K-3 up to the next check, none the last of the call;
+            // the handle's first two such runs (in a precision) go out eagerly:
+            // the capture takes about 0.6 ms, which a solve of one or two blocks
+            // does not get back
+            const int L = K - 2;
+            int &runs = P->graph_runs[P->in_fp32 ? 1 : 0];
             if (done + L < n_iters && P->t + L < P->prm.max_iters) {
-                CHK(run_graph(P, tau, sigma, P->k, L));
-                if (P->in_fp32) P->fp32_iters += L;
-                done += L;
-                P->k += L;
-                P->t += L;
-                continue;
+                if (++runs > 2) {
+                    runs = 3;
+                    CHK(run_graph(P, tau, sigma, P->k, L));
+                    if (P->in_fp32) P->fp32_iters += L;
+                    done += L;
+                    P->k += L;
+                    P->t += L;
+                    continue;
+                }
             }
         }
         const bool last = (done + 1 == n_iters) || (P->t + 1 >= P->prm.max_iters);
@@ -1402,11 +1412,11 @@ static int iterate_impl(dpdlp_problem *P, int64_t n_iters)
         {
             ProfScope ps(P, 4);
             hipLaunchKernelGGL(k_control, dim3(1), dim3(kBlock), 0, P->s, P->part_r, P->chk_nr,
-                               P->part_c, P->chk_nc, P->ctl, ctl_args(P, 0));
+                               P->part_c, P->chk_nc, P->ctl, P->d_ctl, ctl_args(P, 0));
         }
         hipError_t le = hipGetLastError();
         if (le != hipSuccess) return hip_fail(le, "kernel launch");
-        CHK(read_ctl(P));
+        HIPCHK(hipStreamSynchronize(P->s));           // k_control has filled h_ctl
         const Control &C = *P->h_ctl;
         dpdlp_log_rec rec{};
         rec.t = P->t; rec.k = P->k; rec.r = C.r; rec.r0 = C.r0;
@@ -1839,14 +1849,13 @@ int dpdlp_kkt(dpdlp_problem *P, const double *x, const double *y, double tau, in
                            P->dr, P->tmp_m);
     }
     launch_checks<double>(P, P->tmp_n, P->tmp_n, P->tmp_m, P->tmp_m, P->tmp_n, P->tmp_m, tau);
-    // evaluate into a scratch control block so the solver state is untouched
-    HIPCHK(hipMemsetAsync(P->ctl_eval, 0, sizeof(Control), P->s));
+    // evaluate into the host's second block so the solver state is untouched
     CtlArgs a = ctl_args(P, 1);
     hipLaunchKernelGGL(k_control, dim3(1), dim3(kBlock), 0, P->s, P->part_r, P->chk_nr, P->part_c,
-                       P->chk_nc, P->ctl_eval, a);
-    Control h;
-    HIPCHK(hipMemcpyAsync(&h, P->ctl_eval, sizeof(Control), hipMemcpyDeviceToHost, P->s));
+                       P->chk_nc, P->ctl, P->d_ctl + 1, a);
+    HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(P->s));
+    const Control &h = P->h_ctl[1];
     out5[0] = h.r_primal; out5[1] = h.r_dual; out5[2] = h.r_gap; out5[3] = h.obj_p; out5[4] = h.obj_d;
     return DPDLP_OK;
 }
