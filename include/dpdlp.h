@@ -95,11 +95,11 @@ typedef struct dpdlp_params {
     int32_t perm_block;       /* 256: block size of the block-wise random    */
                               /* permutation (Sec. 4.2); 0: no permutation   */
     int32_t tile_nnz;         /* nonzeros per workgroup tile (Sec. 4.3 at CU */
-                              /* granularity), max 2048; 0 = automatic: the  */
-                              /* power of two in [256, 2048] nearest to      */
-                              /* nnz / 800 on a log scale (about 800 tiles   */
-                              /* per step, within one round of 5 resident    */
-                              /* workgroups on each of the 256 CUs)          */
+                              /* granularity), max 2048; 0 = automatic: FP64 */
+                              /* 256 below 100k nonzeros, 512 below 3M, 1024 */
+                              /* below 6M, 2048 beyond; FP32_MIXED the power */
+                              /* of two in [256, 2048] nearest to nnz / 800  */
+                              /* on a log scale                              */
     uint64_t perm_seed;       /* seed of the block permutation               */
     int32_t precision;        /* DPDLP_FP64 or DPDLP_FP32_MIXED              */
     int32_t xcd_remap;        /* 1: map consecutive tiles onto one XCD        */

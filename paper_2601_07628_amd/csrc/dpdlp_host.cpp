@@ -261,13 +261,13 @@ void merge_short_splits(std::vector<Tile> &tiles)
 void choose_sum_widths(std::vector<Tile> &tiles, const int32_t *ptr)
 {
     // threads only where the tiles hold enough segments to pay for starting
-    // them (about 30 us each)
+    // them (about 20 us each)
     const size_t nt = tiles.size();
     int64_t segs = 0;
     for (const Tile &d : tiles) segs += d.seg_end - d.seg_begin;
-    const int nth = (int)std::min<int64_t>(host_threads(), 1 + segs / 65536);
+    const int nth = (int)std::min<int64_t>(host_threads(), 1 + segs / 16384);
     auto work = [&](int t) {
-        std::vector<int32_t> longest((size_t)kMaxSegs + 1);
+        std::vector<int32_t> longest((size_t)kMaxSegs + 4);
         for (size_t i = nt * (size_t)t / nth; i < nt * (size_t)(t + 1) / nth; ++i) {
             Tile &d = tiles[i];
             if (d.npieces != 0) continue;
@@ -283,20 +283,22 @@ void choose_sum_widths(std::vector<Tile> &tiles, const int32_t *ptr)
             // trips: the primal step of a 4M-nonzero LP with such columns
             // took 39 us, now 31; of a uniform 1M-nonzero LP 11.4, now 10.5.
             int best = 6;
-            int64_t best_cost = INT64_MAX;
+            int32_t best_cost = INT32_MAX;            // (at most 1024 groups of 2048 nonzeros)
+            int32_t *const len = longest.data();
             for (int w = 6; w >= 0; --w) {
-                int64_t wave[kBlock / 64] = {0};
-                for (int32_t g = 0; g < groups; ++g) {
-                    const int64_t trips = (longest[(size_t)g] + (1 << w) - 1) >> w;
-                    wave[g % (kBlock / 64)] += (trips < 4 ? 110 * trips : 40 * trips + 200) + 200 + 20 * w;
-                }
-                const int64_t cost = *std::max_element(wave, wave + kBlock / 64);
+                int32_t wave[kBlock / 64] = {0};
+                len[groups] = len[groups + 1] = len[groups + 2] = 0;
+                for (int32_t g = 0; g < groups; g += kBlock / 64)
+                    for (int v = 0; v < kBlock / 64; ++v) {
+                        const int32_t trips = (len[g + v] + (1 << w) - 1) >> w;
+                        wave[v] += std::min(110 * trips, 40 * trips + 200);
+                    }
+                const int32_t cost = *std::max_element(wave, wave + kBlock / 64) +
+                                     (groups + 3) / 4 * (200 + 20 * w);
                 if (cost < best_cost) { best_cost = cost; best = w; }
                 // the next width takes two of these groups together
-                for (int32_t g = 0; g < groups; g += 2)
-                    longest[(size_t)(g / 2)] =
-                        g + 1 < groups ? std::max(longest[(size_t)g], longest[(size_t)g + 1]) : longest[(size_t)g];
                 groups = (groups + 1) / 2;
+                for (int32_t g = 0; g < groups; ++g) len[g] = std::max(len[2 * g], len[2 * g + 1]);
             }
             d.width_log2 |= best << 8;
         }

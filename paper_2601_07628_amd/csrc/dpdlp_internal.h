@@ -74,7 +74,7 @@ void sort_tiles_by_gather(const std::vector<Tile> &tiles, hvec<int32_t> &idx,
 // workgroup walks, so that no launch has to add them up; such tiles come
 // first in each XCD's contiguous run of tiles, so that none of them starts
 // last.  Larger splits stay consecutive tiles.
-constexpr int kMergePieces = 4;
+constexpr int kMergePieces = 8;
 void merge_short_splits(std::vector<Tile> &tiles);
 
 // Width of the FP64 segment sums: for every whole tile the 2^w lanes per

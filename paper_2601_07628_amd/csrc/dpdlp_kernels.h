@@ -837,27 +837,23 @@ struct CheckColOp {
     }
 };
 
-// Plain product with an optional divisor read from device memory:
-//   out_s = sum_p a_p * (in[idx_p] / *div); partial 0 = sum out_s^2.
+// Plain product out[perm[s]] = sum_p a_p in[idx_p] (perm null: out[s]): the
+// caller's order is restored in the same pass (a launch of its own took 4 us).
 struct SpmvOp {
     using MT = double; using AT = double; using R = SumOp;
-    static constexpr int NR = 1, NQ = 1;
+    static constexpr int NR = 1, NQ = 0;
     int slice = 0;
     __device__ void resolve() {}
     const double *__restrict__ in;
-    const double *__restrict__ div;   // may be null
     double *__restrict__ out;
+    const int *__restrict__ perm;
     double *partials;
-    __device__ void value(MT v, int j, AT *o) const
+    __device__ void value(MT v, int j, AT *o) const { o[0] = v * in[j]; }
+    struct Pre { int at; };
+    template <bool NT> __device__ void prefetch(int s, Pre &p) const { p.at = perm ? perm[s] : s; }
+    template <bool NT> __device__ void epilogue(int, const AT *r, const Pre &p, double *) const
     {
-        o[0] = div ? v * (in[j] / *div) : v * in[j];
-    }
-    using Pre = NoPre;
-    template <bool NT> __device__ void prefetch(int, Pre &) const {}
-    template <bool NT> __device__ void epilogue(int s, const AT *r, const Pre &, double *acc) const
-    {
-        out[s] = r[0];
-        acc[0] += r[0] * r[0];
+        out[p.at] = r[0];
     }
 };
 

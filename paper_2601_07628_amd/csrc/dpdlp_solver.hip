@@ -47,11 +47,13 @@ __global__ void k_convert(const Ti *__restrict__ in, To *__restrict__ out, int64
     if (i < n) out[i] = (To)in[i];
 }
 
-// d[i] *= f[i]
-__global__ void k_mul(double *__restrict__ d, const double *__restrict__ f, int n)
+// dr[i] *= fr[i], dc[j] *= fc[j]
+__global__ void k_mul(double *__restrict__ dr, const double *__restrict__ fr, int m,
+                      double *__restrict__ dc, const double *__restrict__ fc, int n)
 {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) d[i] *= f[i];
+    if (i < m) dr[i] *= fr[i];
+    if (i < n) dc[i] *= fc[i];
 }
 
 // Scale the stored values of A by (a * f_row[i]) * f_col[j] over one format's
@@ -69,7 +71,8 @@ __global__ __launch_bounds__(kBlock) void k_scale_vals(const Tile *__restrict__ 
     if (t >= ntiles) return;
     const Tile d = tiles[t];
     const int nseg = d.seg_end - d.seg_begin;
-    const int wl = d.width_log2 & 0xff;
+    // lanes per segment: as the FP64 sums, all for (a piece of) a split segment
+    const int wl = d.npieces ? 8 : d.width_log2 >> 8;
     const int G = 1 << wl;
     const int lane = threadIdx.x & (G - 1);
     for (int s = threadIdx.x >> wl; s < nseg; s += kBlock >> wl) {
@@ -1102,13 +1105,24 @@ static int create_impl(const dpdlp_csr_lp *lp_in, const dpdlp_params *params, vo
     std::unique_ptr<dpdlp_problem> guard(P);
     if (params) P->prm = *params; else dpdlp_params_default(&P->prm);
     if (P->prm.tile_nnz <= 0) {
-        // automatic: the power of two (256..2048) nearest, on a log scale,
-        // to nnz / 800, i.e. about 800 tiles per step where the problem is
-        // small enough: fewer tiles than one round of resident workgroups
-        // (256 CUs x 5), each long enough to hide its memory round trips
-        const double tn = (double)lp.row_ptr[lp.m] / 800.0;
+        const double nz = (double)lp.row_ptr[lp.m];
         int32_t p2 = 256;
-        while (p2 < kTileNnzMax && tn > (double)p2 * 1.4142135623730951) p2 <<= 1;
+        if (P->prm.precision == DPDLP_FP32_MIXED) {
+            // the power of two (256..2048) nearest, on a log scale, to
+            // nnz / 800: about 800 tiles per step where the problem is small
+            // enough (another tile size would group FP32 sums differently)
+            while (p2 < kTileNnzMax && nz / 800.0 > (double)p2 * 1.4142135623730951) p2 <<= 1;
+        } else if (nz >= 1e5) {
+            // few tiles while one round of them leaves CUs idle, small ones
+            // (512: 2 loads of each kind per thread) up to several rounds,
+            // large ones where the matrix stream is what counts.  Measured,
+            // us per iteration at 256 / 512 / 1024 / 2048: 45k nonzeros 6.9 /
+            // 7.4 / 8.1 / 10.7; 280k (skewed columns) 13.4 / 10.1 / 11.8 /
+            // 15.7; 630k 13.6 / 13.3 / 13.7 / 15.2; 1.2M (LASSO) 27.2 / 26.6 /
+            // 27.4 / 30.9; 2.1M 34.4 / 32.7 / 33.1 / 35.5; 4.2M 64.0 / 59.7 /
+            // 58.4 / 60.3; 4.3M (skewed) 69.6 / 65.5 / 64.6 / 64.1
+            p2 = nz < 3e6 ? 512 : nz < 6e6 ? 1024 : 2048;
+        }
         P->prm.tile_nnz = p2;
     }
     if (P->prm.tile_nnz > kTileNnzMax) P->prm.tile_nnz = kTileNnzMax;
@@ -1243,12 +1257,11 @@ static int create_impl(const dpdlp_csr_lp *lp_in, const dpdlp_params *params, vo
         if (P->tc.n)
             hipLaunchKernelGGL(k_scale_vals, dim3(P->tc.n), dim3(kBlock), 0, P->s, P->tc.d, P->tc.n,
                                P->cp, P->ri, P->vt, P->fc, P->fr, 0);
-        hipLaunchKernelGGL(k_mul, dim3(nblk(m)), dim3(kBlock), 0, P->s, P->dr, P->fr, m);
-        hipLaunchKernelGGL(k_mul, dim3(nblk(n)), dim3(kBlock), 0, P->s, P->dc, P->fc, n);
+        hipLaunchKernelGGL(k_mul, dim3(nblk(std::max(m, n))), dim3(kBlock), 0, P->s, P->dr, P->fr, m,
+                           P->dc, P->fc, n);
     };
     for (int it = 0; it < P->prm.ruiz_iters; ++it) {
-        hipLaunchKernelGGL(k_fill<double>, dim3(nblk(m)), dim3(kBlock), 0, P->s, P->fr, 1.0, (int64_t)m);
-        hipLaunchKernelGGL(k_fill<double>, dim3(nblk(n)), dim3(kBlock), 0, P->s, P->fc, 1.0, (int64_t)n);
+        // (every segment, empty ones too, gets its factor)
         AbsMaxOp a; a.f = P->fr; a.partials = nullptr;
         launch_tiles(P, a, P->tr, P->rp, P->ci, P->v);
         AbsMaxOp b; b.f = P->fc; b.partials = nullptr;
@@ -1800,20 +1813,15 @@ int dpdlp_spmv(dpdlp_problem *P, int32_t transpose, const double *in, double *ou
 {
     ENTER(P);
     if (!in || !out) { set_error("NULL vector"); return DPDLP_E_INVALID_ARG; }
-    const int32_t m = P->m, n = P->n;
-    const int kin = transpose ? m : n, kout = transpose ? n : m;
+    const int kin = transpose ? P->m : P->n;
     double *pin = transpose ? P->tmp_m2 : P->tmp_n2;
-    double *pout = transpose ? P->tmp_n : P->tmp_m;
     hipLaunchKernelGGL(k_permute<double>, dim3(nblk(kin)), dim3(kBlock), 0, P->s, kin, in,
                        transpose ? P->perm_row : P->perm_col, (const double *)nullptr, pin);
-    SpmvOp op; op.in = pin; op.div = nullptr; op.out = pout;
-    op.partials = transpose ? P->part_c : P->part_r;
+    SpmvOp op; op.in = pin; op.out = out; op.partials = nullptr;
+    op.perm = transpose ? P->perm_col : P->perm_row;
     launch_product(P, transpose != 0, op, pin);
-    hipLaunchKernelGGL(k_unpermute<double>, dim3(nblk(kout)), dim3(kBlock), 0, P->s, kout, pout,
-                       transpose ? P->perm_col : P->perm_row, (const double *)nullptr, out);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(P->s));
-    (void)kout;
     return DPDLP_OK;
 }
 
@@ -1905,10 +1913,10 @@ int dpdlp_time_kernel(dpdlp_problem *P, int32_t which, int32_t reps, void *strea
                                         P->v32, sigma, 5, 0);
             else launch_dual<double>(P, P->xbar, P->clo, P->chi, P->ya, P->tmp_m, P->v, sigma, 5, 0);
         } else if (which == 2) {
-            SpmvOp op; op.in = P->x; op.div = nullptr; op.out = P->tmp_m; op.partials = P->part_r;
+            SpmvOp op; op.in = P->x; op.out = P->tmp_m; op.perm = nullptr; op.partials = nullptr;
             launch_product(P, false, op, P->x);
         } else {
-            SpmvOp op; op.in = P->y; op.div = nullptr; op.out = P->tmp_n; op.partials = P->part_c;
+            SpmvOp op; op.in = P->y; op.out = P->tmp_n; op.perm = nullptr; op.partials = nullptr;
             launch_product(P, true, op, P->y);
         }
     };

@@ -61,7 +61,7 @@ def test_long_segments_among_short_ones(D, O, long_len):  # noqa: F811
 @pytest.mark.parametrize("slices", [0, 8])
 @pytest.mark.parametrize("pieces", [1, 2, 4, 5, 12])
 def test_split_segments_merged_and_not(D, O, pieces, slices):  # noqa: F811
-    """Rows of `pieces` tiles among short ones: up to four pieces stay in one
+    """Rows of `pieces` tiles among short ones: up to eight pieces stay in one
     workgroup, more are added up by a launch of their own (unsliced) or by the
     combine (sliced); with rows of both kinds in one matrix."""
     rng = np.random.default_rng(10 * pieces + slices)
