@@ -258,7 +258,7 @@ void merge_short_splits(std::vector<Tile> &tiles)
     }
 }
 
-void choose_sum_widths(std::vector<Tile> &tiles, const int32_t *ptr)
+void choose_sum_lanes(std::vector<Tile> &tiles, const int32_t *ptr)
 {
     // threads only where the tiles hold enough segments to pay for starting
     // them (about 20 us each)
@@ -268,39 +268,50 @@ void choose_sum_widths(std::vector<Tile> &tiles, const int32_t *ptr)
     const int nth = (int)std::min<int64_t>(host_threads(), 1 + segs / 16384);
     auto work = [&](int t) {
         std::vector<int32_t> longest((size_t)kMaxSegs + 4);
+        int32_t *const len = longest.data();
         for (size_t i = nt * (size_t)t / nth; i < nt * (size_t)(t + 1) / nth; ++i) {
             Tile &d = tiles[i];
             if (d.npieces != 0) continue;
             int32_t groups = d.seg_end - d.seg_begin;
-            for (int32_t s = 0; s < groups; ++s)
-                longest[(size_t)s] = ptr[d.seg_begin + s + 1] - ptr[d.seg_begin + s];
-            // a wave's lanes work on 64 >> w segments at a time and wait for
-            // the longest: single trips of G nonzeros, from 4 on with 4 reads
-            // in flight, a fixed part for the pointers and one step per
-            // halving (LDS latency about 100 cycles, a lane permutation about
-            // 20).  With the width of the mean length, one column of 1500
-            // among columns of 1 to 3 nonzeros kept 16 lanes busy for 94
-            // trips: the primal step of a 4M-nonzero LP with such columns
-            // took 39 us, now 31; of a uniform 1M-nonzero LP 11.4, now 10.5.
-            int best = 6;
-            int32_t best_cost = INT32_MAX;            // (at most 1024 groups of 2048 nonzeros)
-            int32_t *const len = longest.data();
+            for (int32_t s = 0; s < groups; ++s) len[s] = ptr[d.seg_begin + s + 1] - ptr[d.seg_begin + s];
+            // The modelled time of the slowest of the tile's four waves, for w
+            // = 6 .. 0 (2^w lanes per segment, so 64 >> w segments at a time
+            // that wait for the longest): a fixed part for the pointers and
+            // one lane permutation per halving, and per trip an LDS round
+            // trip (about 100 cycles), 4 of them in flight for 4 or more.
+            // Lanes of the order's own width W, or 2^h sums per lane on W - h:
+            // one trip per 2^W nonzeros, its 2^h reads in flight.
+            const int W = d.width_log2;
+            int best_h = 0, best_w = W;
+            int32_t h_cost = INT32_MAX, w_cost = INT32_MAX;   // (at most 1024 groups of 2048 nonzeros)
             for (int w = 6; w >= 0; --w) {
-                int32_t wave[kBlock / 64] = {0};
+                int32_t own[kBlock / 64] = {0}, wave[kBlock / 64] = {0};
+                const int h = W - w;
+                const int32_t trip = h >= 0 ? 100 + 12 * (1 << std::min(h, 2)) : 0;
                 len[groups] = len[groups + 1] = len[groups + 2] = 0;
                 for (int32_t g = 0; g < groups; g += kBlock / 64)
                     for (int v = 0; v < kBlock / 64; ++v) {
                         const int32_t trips = (len[g + v] + (1 << w) - 1) >> w;
                         wave[v] += std::min(110 * trips, 40 * trips + 200);
+                        own[v] += ((len[g + v] + (1 << W) - 1) >> W) * trip;
                     }
-                const int32_t cost = *std::max_element(wave, wave + kBlock / 64) +
-                                     (groups + 3) / 4 * (200 + 20 * w);
-                if (cost < best_cost) { best_cost = cost; best = w; }
+                const int32_t fixed = (groups + 3) / 4 * (200 + 20 * w);
+                const int32_t wide = *std::max_element(wave, wave + kBlock / 64) + fixed;
+                if (wide < w_cost) { w_cost = wide; best_w = w; }
+                if (h >= 0 && h <= 2) {
+                    const int32_t c = h == 0 ? wide : *std::max_element(own, own + kBlock / 64) + fixed + (groups + 3) / 4 * 10 * h;
+                    if (c < h_cost) { h_cost = c; best_h = h; }
+                }
                 // the next width takes two of these groups together
                 groups = (groups + 1) / 2;
                 for (int32_t g = 0; g < groups; ++g) len[g] = std::max(len[2 * g], len[2 * g + 1]);
             }
-            d.width_log2 |= best << 8;
+            d.width_log2 |= best_h << 8;
+            // another order of additions only where it saves 5%.  One
+            // column of 1500 among columns of 1 to 3 nonzeros kept 16 lanes
+            // busy for 94 trips: the primal step of a 4M-nonzero LP with such
+            // columns took 39 us with the lanes of the mean length, 31 with these
+            if (20 * (int64_t)w_cost < 19 * (int64_t)h_cost) d.width_log2 |= (best_w + 1) << 12;
         }
     };
     if (nth == 1) work(0);
@@ -528,7 +539,7 @@ void slice_format(const hvec<int32_t> &ptr, const hvec<int32_t> &idx, const hvec
             out.tiles.push_back(t);
         }
     }
-    choose_sum_widths(out.tiles, out.ptr.data());
+    choose_sum_lanes(out.tiles, out.ptr.data());
 }
 
 void permute_and_transpose(const dpdlp_csr_lp *lp, int32_t block, uint64_t seed,

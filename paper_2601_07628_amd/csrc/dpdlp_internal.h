@@ -77,10 +77,11 @@ void sort_tiles_by_gather(const std::vector<Tile> &tiles, hvec<int32_t> &idx,
 constexpr int kMergePieces = 8;
 void merge_short_splits(std::vector<Tile> &tiles);
 
-// Width of the FP64 segment sums: for every whole tile the 2^w lanes per
-// segment with the least modelled time of the tile's four waves goes into
-// bits 8.. of width_log2 (bits 0-7 keep the width from the mean length).
-void choose_sum_widths(std::vector<Tile> &tiles, const int32_t *ptr);
+// Lanes of the segment sums of every whole tile: width_log2 holds, beside the
+// W of the order of additions (bits 0-7), the h of 2^(W - h) lanes per segment
+// (bits 8-11) and, where the FP64 sums take another order with w lanes, w + 1
+// (bits 12-15).
+void choose_sum_lanes(std::vector<Tile> &tiles, const int32_t *ptr);
 
 void slice_bounds(const hvec<int32_t> &gptr, int32_t nidx, int32_t S,
                   std::vector<int32_t> &bounds);

@@ -36,6 +36,7 @@
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "dpdlp_internal.h"
 
@@ -289,41 +290,71 @@ __global__ __launch_bounds__(kBlock) void k_tile(const Tile *__restrict__ tiles,
     for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
 
     if (whole) {
-        // 2. segment reductions by groups of G lanes; a segment's result
-        // replaces its first product (only its own group reads that range)
-        // (FP32 sums keep the width of their first layout: another order of
-        // additions would change results in their last bits)
-        const int wl = (sizeof(AT) == 8 ? d.width_log2 >> 8 : d.width_log2) & 0xff;
-        const int G = 1 << wl;
-        const int lane = threadIdx.x & (G - 1);
-        const int ngrp = kBlock >> wl;
-        for (int s = threadIdx.x >> wl; s < nseg; s += ngrp) {
-            const int b = s_ptr[s], e = s_ptr[s + 1];
-            AT r[NR];
+        // 2. segment sums; a segment's result replaces its first product (only
+        // its own lanes read that range).  The order of a sum is that of 2^W
+        // strided partial sums and a butterfly over them; 2^(W - h) lanes take
+        // a segment, 2^h partial sums each, and the butterfly's first h steps
+        // are additions inside a lane: the same sums, with fewer passes over
+        // the tile's segments (choose_sum_lanes picks h, and in FP64 another W
+        // where a long segment would keep the others waiting).
+        const int wide = sizeof(AT) == 8 ? (d.width_log2 >> 12) & 15 : 0;
+        const int W = wide ? wide - 1 : d.width_log2 & 15;
+        auto sums = [&](auto h_) {
+            constexpr int H = decltype(h_)::value, A = 1 << H;
+            const int wl = W - H;
+            const int lane = threadIdx.x & ((1 << wl) - 1);
+            for (int s = threadIdx.x >> wl; s < nseg; s += kBlock >> wl) {
+                const int b = s_ptr[s], e = s_ptr[s + 1];
+                AT r[A][NR];
 #pragma unroll
-            for (int q = 0; q < NR; ++q) r[q] = R::template id<AT>();
-            int p = b + lane;
-            for (; p + 3 * G < e; p += 4 * G) {       // 4 reads in flight, added in order
-                AT w[4][NR];
+                for (int u = 0; u < A; ++u)
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
+                    for (int q = 0; q < NR; ++q) r[u][q] = R::template id<AT>();
+                int p = b + lane;
+                if constexpr (H == 0) {
+                    const int G = 1 << wl;
+                    for (; p + 3 * G < e; p += 4 * G) {       // 4 reads in flight, added in order
+                        AT w[4][NR];
 #pragma unroll
-                    for (int q = 0; q < NR; ++q) w[u][q] = s_prod[q][p + u * G];
+                        for (int u = 0; u < 4; ++u)
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
+                            for (int q = 0; q < NR; ++q) w[u][q] = s_prod[q][p + u * G];
 #pragma unroll
-                    for (int q = 0; q < NR; ++q) r[q] = R::comb(r[q], w[u][q]);
+                        for (int u = 0; u < 4; ++u)
+#pragma unroll
+                            for (int q = 0; q < NR; ++q) r[0][q] = R::comb(r[0][q], w[u][q]);
+                    }
+                }
+                for (; p < e; p += 1 << W) {
+                    AT w[A][NR];
+#pragma unroll
+                    for (int u = 0; u < A; ++u)
+#pragma unroll
+                        for (int q = 0; q < NR; ++q) w[u][q] = s_prod[q][min(p + (u << wl), e - 1)];
+#pragma unroll
+                    for (int u = 0; u < A; ++u)
+#pragma unroll
+                        for (int q = 0; q < NR; ++q)
+                            r[u][q] = p + (u << wl) < e ? R::comb(r[u][q], w[u][q]) : r[u][q];
+                }
+#pragma unroll
+                for (int o = A / 2; o > 0; o >>= 1)
+#pragma unroll
+                    for (int u = 0; u < o; ++u)
+#pragma unroll
+                        for (int q = 0; q < NR; ++q) r[u][q] = R::comb(r[u][q], r[u + o][q]);
+#pragma unroll
+                for (int q = 0; q < NR; ++q) r[0][q] = group_reduce<R>(r[0][q], wl);
+                if (lane == 0 && e > b) {
+#pragma unroll
+                    for (int q = 0; q < NR; ++q) s_prod[q][b] = r[0][q];
+                }
             }
-            for (; p < e; p += G) {
-#pragma unroll
-                for (int q = 0; q < NR; ++q) r[q] = R::comb(r[q], s_prod[q][p]);
-            }
-#pragma unroll
-            for (int q = 0; q < NR; ++q) r[q] = group_reduce<R>(r[q], wl);
-            if (lane == 0 && e > b) {
-#pragma unroll
-                for (int q = 0; q < NR; ++q) s_prod[q][b] = r[q];
-            }
+        };
+        switch (wide ? 0 : (d.width_log2 >> 8) & 15) {
+        case 0: sums(std::integral_constant<int, 0>{}); break;
+        case 1: sums(std::integral_constant<int, 1>{}); break;
+        default: sums(std::integral_constant<int, 2>{}); break;
         }
         __syncthreads();
         // 3. fused epilogue, one thread per segment (coalesced vector I/O)

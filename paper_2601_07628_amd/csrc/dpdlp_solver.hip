@@ -72,7 +72,8 @@ __global__ __launch_bounds__(kBlock) void k_scale_vals(const Tile *__restrict__ 
     const Tile d = tiles[t];
     const int nseg = d.seg_end - d.seg_begin;
     // lanes per segment: as the FP64 sums, all for (a piece of) a split segment
-    const int wl = d.npieces ? 8 : d.width_log2 >> 8;
+    const int wide = d.width_log2 >> 12;
+    const int wl = d.npieces ? 8 : wide ? wide - 1 : (d.width_log2 & 15) - ((d.width_log2 >> 8) & 15);
     const int G = 1 << wl;
     const int lane = threadIdx.x & (G - 1);
     for (int s = threadIdx.x >> wl; s < nseg; s += kBlock >> wl) {
@@ -817,7 +818,7 @@ static int build_tileset(dpdlp_problem *P, const hvec<int32_t> &ptr, int32_t nse
         if (t.npieces > 0 && t.piece == 0) sp.push_back(SplitSeg{t.seg_begin, i, t.npieces, t.slice});
     }
     ts.nsplit = (int)sp.size();
-    choose_sum_widths(host_tiles, ptr.data());
+    choose_sum_lanes(host_tiles, ptr.data());
     CHK(dalloc(P, &ts.d, host_tiles.size()));
     CHK(upload(P, ts.d, host_tiles.data(), host_tiles.size() * sizeof(Tile)));
     if (ts.nsplit) {
