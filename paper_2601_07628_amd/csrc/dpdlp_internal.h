@@ -12,7 +12,9 @@
 
 namespace dpdlp {
 
-// Tile descriptor: 8 int32 (see dpdlp_build_tiles).
+// Tile descriptor: 8 int32 (see dpdlp_build_tiles; on the device width_log2
+// also holds what choose_sum_lanes adds, and npieces < 0 marks the tiles that
+// merge_short_splits makes).
 struct Tile {
     int32_t seg_begin, seg_end, nnz_begin, nnz_end;
     int32_t width_log2, piece, npieces, slice;   // slice: gather slice (sliced sets)

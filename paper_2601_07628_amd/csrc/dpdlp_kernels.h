@@ -6,12 +6,13 @@
 // columns) is cut on the host into tiles of at most kTileNnzMax nonzeros
 // (nonzero-aware partitioning, Sec. 4.3 of the D-PDLP paper, applied to
 // workgroups).  One workgroup owns one tile:
-//   1. it streams the tile's (index, value) pairs once with coalesced
-//      non-temporal loads, gathers the vector entry, and stages the products
-//      in LDS;
-//   2. groups of G = 2^width_log2 lanes (G chosen per tile from the mean
-//      segment length) reduce one segment each from LDS with a fixed-order
-//      strided sum and an xor-shuffle butterfly;
+//   1. it streams the tile's (index, value) pairs once with coalesced loads
+//      (non-temporal where the data exceed the Infinity Cache), gathers the
+//      vector entry, and stages the products in LDS;
+//   2. groups of lanes reduce one segment each from LDS in the order of a
+//      2^W-strided sum and a butterfly (W per tile from the mean segment
+//      length; the lanes per tile from a model of its waves' time), with lane
+//      permutations of the vector ALU;
 //   3. one thread per segment applies the fused epilogue (projection,
 //      reflection, Halpern, or a residual contribution) with coalesced
 //      vector loads and stores.
@@ -21,10 +22,11 @@
 // neighbouring entries together; pos then gives every nonzero's position in
 // the tile's segment order, where its product is stored in LDS, so the
 // segment sums are unchanged.
-// A segment longer than a tile is split into pieces; each piece's workgroup
-// reduces its part and publishes it, and a small follow-up kernel adds the
-// pieces in piece order and runs the epilogue.  The summation order is fixed
-// by the tiling alone, so results are bitwise reproducible run to run.
+// A segment longer than a tile is split into pieces.  Up to kMergePieces of
+// them stay in one workgroup, one after another; otherwise each piece's
+// workgroup publishes its part and the pieces are added in piece order by the
+// sliced step's combine, or by a small follow-up kernel.  The summation order
+// is fixed by the tiling alone, so results are bitwise reproducible run to run.
 //
 // The XCD-sliced form (the paper's 2-D partition, Sec. 3.1 / App. D, across
 // the 8 XCDs): the gathered dimension is cut into S slices, slice s runs on

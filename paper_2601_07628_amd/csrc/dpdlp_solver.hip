@@ -10,8 +10,8 @@
 // CSC check pass then produce per-tile partial sums, and a single-workgroup
 // control kernel adds them in a fixed order and takes, in FP64 on the
 // device, the KKT (App. B.4), restart (App. B.2) and PID primal-weight
-// (App. B.3) decisions.  The host reads back a ~200-byte control block per
-// check to schedule the next launches.
+// (App. B.3) decisions.  It writes its ~200-byte control block to pinned host
+// memory too, from which the host schedules the next launches.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
