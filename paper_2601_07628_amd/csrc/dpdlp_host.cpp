@@ -273,7 +273,11 @@ void choose_sum_lanes(std::vector<Tile> &tiles, const int32_t *ptr)
             Tile &d = tiles[i];
             if (d.npieces != 0) continue;
             int32_t groups = d.seg_end - d.seg_begin;
-            for (int32_t s = 0; s < groups; ++s) len[s] = ptr[d.seg_begin + s + 1] - ptr[d.seg_begin + s];
+            int32_t most = 0;
+            for (int32_t s = 0; s < groups; ++s) {
+                len[s] = ptr[d.seg_begin + s + 1] - ptr[d.seg_begin + s];
+                most = std::max(most, len[s]);
+            }
             // The modelled time of the slowest of the tile's four waves, for w
             // = 6 .. 0 (2^w lanes per segment, so 64 >> w segments at a time
             // that wait for the longest): a fixed part for the pointers and
@@ -284,7 +288,15 @@ void choose_sum_lanes(std::vector<Tile> &tiles, const int32_t *ptr)
             const int W = d.width_log2;
             int best_h = 0, best_w = W;
             int32_t h_cost = INT32_MAX, w_cost = INT32_MAX;   // (at most 1024 groups of 2048 nonzeros)
+            // (many more lanes than the mean length's only for a long segment)
+            const int top = most > 8 << W ? 6 : std::min(6, W + 1);
             for (int w = 6; w >= 0; --w) {
+                if (w > top) {
+                    len[groups] = 0;
+                    groups = (groups + 1) / 2;
+                    for (int32_t g = 0; g < groups; ++g) len[g] = std::max(len[2 * g], len[2 * g + 1]);
+                    continue;
+                }
                 int32_t own[kBlock / 64] = {0}, wave[kBlock / 64] = {0};
                 const int h = W - w;
                 const int32_t trip = h >= 0 ? 100 + 12 * (1 << std::min(h, 2)) : 0;

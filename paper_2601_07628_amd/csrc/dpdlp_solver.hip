@@ -71,9 +71,9 @@ __global__ __launch_bounds__(kBlock) void k_scale_vals(const Tile *__restrict__ 
     if (t >= ntiles) return;
     const Tile d = tiles[t];
     const int nseg = d.seg_end - d.seg_begin;
-    // lanes per segment: as the FP64 sums, all for (a piece of) a split segment
-    const int wide = d.width_log2 >> 12;
-    const int wl = d.npieces ? 8 : wide ? wide - 1 : (d.width_log2 & 15) - ((d.width_log2 >> 8) & 15);
+    // lanes per segment: W (fewer would read in shorter runs), more where a long
+    // segment is among them, all for (a piece of) a split segment
+    const int wl = d.npieces ? 8 : max(d.width_log2 & 15, (d.width_log2 >> 12) - 1);
     const int G = 1 << wl;
     const int lane = threadIdx.x & (G - 1);
     for (int s = threadIdx.x >> wl; s < nseg; s += kBlock >> wl) {
