@@ -263,8 +263,16 @@ void choose_sum_lanes(std::vector<Tile> &tiles, const int32_t *ptr)
     // threads only where the tiles hold enough segments to pay for starting
     // them (about 20 us each)
     const size_t nt = tiles.size();
-    int64_t segs = 0;
-    for (const Tile &d : tiles) segs += d.seg_end - d.seg_begin;
+    int64_t segs = 0, nnz = 0;
+    for (const Tile &d : tiles) {
+        segs += d.seg_end - d.seg_begin;
+        nnz += d.nnz_end - d.nnz_begin;
+    }
+    // several rounds of workgroups hide the latency that 2^h reads at once
+    // save, and their unused reads cost LDS bandwidth: from 6M nonzeros on
+    // FP64 takes the other order always (64 iterations on 40M: 38.5 ms
+    // against 38.9; on 10M 10.30 against 10.35)
+    const bool large = nnz >= 6000000;
     const int nth = (int)std::min<int64_t>(host_threads(), 1 + segs / 16384);
     auto work = [&](int t) {
         std::vector<int32_t> longest((size_t)kMaxSegs + 4);
@@ -323,7 +331,7 @@ void choose_sum_lanes(std::vector<Tile> &tiles, const int32_t *ptr)
             // column of 1500 among columns of 1 to 3 nonzeros kept 16 lanes
             // busy for 94 trips: the primal step of a 4M-nonzero LP with such
             // columns took 39 us with the lanes of the mean length, 31 with these
-            if (20 * (int64_t)w_cost < 19 * (int64_t)h_cost) d.width_log2 |= (best_w + 1) << 12;
+            if (large || 20 * (int64_t)w_cost < 19 * (int64_t)h_cost) d.width_log2 |= (best_w + 1) << 12;
         }
     };
     if (nth == 1) work(0);
