@@ -110,6 +110,20 @@ constexpr int kMaxSegs = DPDLP_TILE_SEGS_MAX;     // segments per tile
 
 void set_error(const std::string &msg);
 
+// The nonzeros begin + first, begin + first + s, ... < end of a segment, s per
+// step.  Unsigned: the last step passes the end by up to s - 1, and positions
+// reach 2^31 - 1, where an int would wrap to a negative position below the end.
+struct Walk {
+    uint32_t p, end;
+    constexpr Walk(int32_t begin_, int32_t end_, uint32_t first)
+        : p((uint32_t)begin_ + first), end((uint32_t)end_)
+    {
+    }
+    constexpr bool has(uint32_t ahead = 0) const { return p + ahead < end; }
+    constexpr int32_t left() const { return (int32_t)(end - p); }   // where has()
+    constexpr void step(uint32_t s) { p += s; }
+};
+
 // The two memory kinds of the C ABI.  Any other value is rejected before a
 // pointer is touched (a host pointer read as device memory would fault).
 inline bool mem_kind_ok(int32_t k) { return k == DPDLP_MEM_HOST || k == DPDLP_MEM_DEVICE; }

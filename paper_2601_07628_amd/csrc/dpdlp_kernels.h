@@ -406,8 +406,9 @@ __global__ __launch_bounds__(kBlock) void k_tile(const Tile *__restrict__ tiles,
     AT tot[NR];
 #pragma unroll
     for (int q = 0; q < NR; ++q) tot[q] = R::comb(R::template id<AT>(), pr[q]);
-    for (int pb = nnz0 + cnt; pb < d.nnz_end; pb += d.piece) {
-        const int pc = min(d.piece, d.nnz_end - pb);
+    for (Walk w(nnz0, d.nnz_end, cnt); w.has(); w.step(d.piece)) {
+        const uint32_t pb = w.p;
+        const int pc = min(d.piece, w.left());
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             const int e = min((int)threadIdx.x + q * kBlock, pc - 1);

@@ -80,9 +80,9 @@ __global__ __launch_bounds__(kBlock) void k_scale_vals(const Tile *__restrict__ 
         const int seg = d.seg_begin + s;
         const int b = max(seg_ptr[seg], d.nnz_begin), e = min(seg_ptr[seg + 1], d.nnz_end);
         const double fs = fseg[seg];
-        for (int p = b + lane; p < e; p += G) {
-            const double fi = fidx[idx[p]];
-            val[p] = csr ? val[p] * fs * fi : val[p] * fi * fs;
+        for (Walk w(b, e, lane); w.has(); w.step(G)) {
+            const double fi = fidx[idx[w.p]];
+            val[w.p] = csr ? val[w.p] * fs * fi : val[w.p] * fi * fs;
         }
     }
 }
