@@ -114,18 +114,20 @@ __device__ __forceinline__ double strided_dot(const double *__restrict__ val,
                                               const double *__restrict__ v, int b, int e, int lane)
 {
     double s = 0.0;
-    for (int p = b + lane; p < e; p += 4 * L) {
+    for (dpdlp::Walk w(b, e, lane); w.has(); w.step(4 * L)) {
+        const int32_t *wi = idx + w.p;
+        const double *wa = val + w.p;
         double a[4] = {0.0, 0.0, 0.0, 0.0}, x[4] = {0.0, 0.0, 0.0, 0.0};
         int k[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (p + u * L < e) { k[u] = idx[p + u * L]; a[u] = val[p + u * L]; }
+            if (w.has(u * L)) { k[u] = wi[u * L]; a[u] = wa[u * L]; }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (p + u * L < e) x[u] = v[k[u]];
+            if (w.has(u * L)) x[u] = v[k[u]];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            if (p + u * L < e) s += a[u] * x[u];
+            if (w.has(u * L)) s += a[u] * x[u];
     }
     return s;
 }
