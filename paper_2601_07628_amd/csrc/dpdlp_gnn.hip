@@ -507,15 +507,15 @@ __device__ __forceinline__ void spmm_segment(const int *__restrict__ idx, const 
 {
     const int l = threadIdx.x & 15;
     in += 16 * (threadIdx.x & (LPS - 1));
-    while (__any(p < pe)) {
+    for (Walk w(p, pe, 0); __any(w.has()); w.step(16)) {
         uint32_t j = 0, a = 0;
-        if (p + l < pe) {
-            j = (uint32_t)idx[p + l];
-            a = __float_as_uint(val[p + l]);
+        if (w.has(l)) {
+            j = (uint32_t)idx[w.p + l];
+            a = __float_as_uint(val[w.p + l]);
         }
         auto half = [&](auto h) {
             constexpr int B = decltype(h)::value * 8;
-            if (!__any(p + B < pe)) return;
+            if (!__any(w.has(B))) return;
             const uint32_t jb[8] = {row_bcast<B>(j), row_bcast<B + 1>(j), row_bcast<B + 2>(j),
                                     row_bcast<B + 3>(j), row_bcast<B + 4>(j), row_bcast<B + 5>(j),
                                     row_bcast<B + 6>(j), row_bcast<B + 7>(j)};
@@ -527,11 +527,10 @@ __device__ __forceinline__ void spmm_segment(const int *__restrict__ idx, const 
             for (int u = 0; u < 8; ++u) r[u] = *(const uint4 *)(in + (long)jb[u] * in_bytes);
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                if (p + B + u < pe) fma8(__uint_as_float(ab[u]), r[u]);
+                if (w.has(B + u)) fma8(__uint_as_float(ab[u]), r[u]);
         };
         half(std::integral_constant<int, 0>{});
         half(std::integral_constant<int, 1>{});
-        p += 16;
     }
 }
 
