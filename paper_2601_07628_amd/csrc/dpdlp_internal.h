@@ -107,6 +107,17 @@ constexpr int kBlock = 256;          // threads per workgroup (4 wave64)
 #endif
 constexpr int kTileNnzMax = DPDLP_TILE_NNZ_MAX;   // products staged in LDS per tile
 constexpr int kMaxSegs = DPDLP_TILE_SEGS_MAX;     // segments per tile
+// positions inside a tile are 16 bits (gather-sorted tiles)
+static_assert(kTileNnzMax >= 1 && kTileNnzMax <= 65536 && kMaxSegs >= 1, "tile limits");
+
+// Nonzeros per thread of the tile kernel for tiles of at most tile_nnz: the
+// instantiation (1, 2, 4, 8, or what the largest tile needs) with the fewest.
+constexpr int kTileLoadsMax = (kTileNnzMax + kBlock - 1) / kBlock > 8 ? (kTileNnzMax + kBlock - 1) / kBlock : 8;
+constexpr int tile_loads(int tile_nnz)
+{
+    const int per = (tile_nnz + kBlock - 1) / kBlock;
+    return per <= 1 ? 1 : per <= 2 ? 2 : per <= 4 ? 4 : per <= 8 ? 8 : kTileLoadsMax;
+}
 
 void set_error(const std::string &msg);
 

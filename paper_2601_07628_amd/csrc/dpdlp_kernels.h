@@ -184,7 +184,7 @@ __device__ __forceinline__ void nt_store(T *p, T v)
 // Memory-level parallelism: every thread first issues all of its index /
 // value loads, the segment-pointer loads and the epilogue prefetches, then
 // all of its gathers, so one tile costs about two memory round trips before
-// the LDS phases.  PER is the tile size over the 256 threads (1, 2, 4 or 8):
+// the LDS phases.  PER is the tile size over the 256 threads (tile_loads()):
 // a small tile issues no repeated loads and takes little LDS.  With PER = 8
 // for every tile size, shuffles through LDS in the segment sums and an LDS
 // buffer of their results, an iteration of a 10k-nonzero LP took 10.3 us

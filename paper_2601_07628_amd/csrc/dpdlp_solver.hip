@@ -526,14 +526,15 @@ static void launch_tiles(dpdlp_problem *P, const Op &op, const TileSet &ts, cons
                            per_xcd, idx, val, seg_ptr, ts.seg_stride, (const uint16_t *)ts.pos,
                            (typename Op::AT *)P->carries, op);
     };
-    // nonzeros per thread: as many as the largest tile needs
-    const int per = (P->prm.tile_nnz + kBlock - 1) / kBlock;
     auto pick = [&](auto nt) {
         constexpr bool NT = decltype(nt)::value;
-        if (per <= 1) go(k_tile<Op, 1, NT>);
-        else if (per <= 2) go(k_tile<Op, 2, NT>);
-        else if (per <= 4) go(k_tile<Op, 4, NT>);
-        else go(k_tile<Op, 8, NT>);
+        switch (tile_loads(P->prm.tile_nnz)) {
+        case 1: go(k_tile<Op, 1, NT>); break;
+        case 2: go(k_tile<Op, 2, NT>); break;
+        case 4: go(k_tile<Op, 4, NT>); break;
+        case 8: go(k_tile<Op, 8, NT>); break;
+        default: go(k_tile<Op, kTileLoadsMax, NT>); break;   // (DPDLP_TILE_NNZ_MAX above 2048)
+        }
     };
     if (streams_fit_cache(P)) pick(std::false_type{});
     else pick(std::true_type{});

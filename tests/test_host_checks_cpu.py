@@ -28,3 +28,9 @@ def run_check(tmp_path, prog, *flags):
 
 def test_walks_end_at_the_largest_positions(tmp_path):
     run_check(tmp_path, "walk_check")
+
+
+@pytest.mark.parametrize("nnz_max,segs_max", [(2048, 1024), (1000, 300), (4096, 1024), (5000, 4096)])
+def test_tile_kernel_holds_every_tile_size(tmp_path, nnz_max, segs_max):
+    run_check(tmp_path, "tile_limits_check", f"-DDPDLP_TILE_NNZ_MAX={nnz_max}",
+              f"-DDPDLP_TILE_SEGS_MAX={segs_max}")
