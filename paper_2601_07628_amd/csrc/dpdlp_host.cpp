@@ -229,11 +229,20 @@ void build_tiles(const int32_t *ptr, int32_t nseg, int32_t tile_nnz,
 
 void merge_short_splits(std::vector<Tile> &tiles)
 {
+    int64_t whole = 0, beside = 0, many = 0;      // whole tiles, segments by pieces
+    for (const Tile &t : tiles) {
+        if (t.npieces == 0) ++whole;
+        else if (t.piece == 0 && t.npieces > kMergeAlways && t.npieces <= kMergeMany)
+            ++(t.npieces <= kMergeBeside ? beside : many);
+    }
+    const int limit = many >= kMergeSegs && whole >= kMergeFull ? kMergeMany
+                      : 4 * whole + beside >= kMergeWhole       ? kMergeBeside
+                                                                : kMergeAlways;
     std::vector<Tile> out;
     bool merged = false;
     for (size_t i = 0; i < tiles.size(); ++i) {
         Tile t = tiles[i];
-        if (t.npieces > 0 && t.npieces <= kMergePieces) {
+        if (t.npieces > 0 && t.npieces <= limit) {
             const int np = t.npieces;
             t.piece = t.nnz_end - t.nnz_begin;
             t.nnz_end = tiles[i + (size_t)np - 1].nnz_end;

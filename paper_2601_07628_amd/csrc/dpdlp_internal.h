@@ -68,15 +68,29 @@ int64_t tile_gather_lines(const std::vector<Tile> &tiles, const hvec<int32_t> &i
 void sort_tiles_by_gather(const std::vector<Tile> &tiles, hvec<int32_t> &idx,
                           hvec<int32_t> &src, hvec<uint16_t> &pos);
 
-// Slices are S contiguous ranges of the gathered index that hold about
-// nnz / S nonzeros each; gptr[nidx + 1] is the gathered dimension's own
-// pointer array (its nonzero counts as prefix sums).
-// Unsliced tile sets: the pieces of a segment split into at most kMergePieces
-// become one tile (npieces = -pieces, piece = nonzeros per piece) that one
-// workgroup walks, so that no launch has to add them up; such tiles come
-// first in each XCD's contiguous run of tiles, so that none of them starts
-// last.  Larger splits stay consecutive tiles.
-constexpr int kMergePieces = 8;
+// Unsliced tile sets: the pieces of a segment split into few become one tile
+// (npieces = -pieces, piece = nonzeros per piece) that one workgroup walks, so
+// that no launch has to add them up; such tiles come first in each XCD's
+// contiguous run of tiles, so that none of them starts last.  Other splits
+// stay consecutive tiles.
+// The walk is a serial chain.  Up to kMergeAlways pieces take no longer than
+// the launch that adds them up; more have to hide behind other tiles: up to
+// kMergeBeside where such segments and four times the whole tiles make
+// kMergeWhole, up to kMergeMany where kMergeSegs segments of more than
+// kMergeBeside are among kMergeFull whole tiles.  Us per iteration, separate /
+// merged, R rows of P pieces among S rows of 5 nonzeros, FP64 where not said:
+//   P 4: R 40, S 0 8.3 / 8.2; R 400, S 0 11.2 / 10.7; R 8, S 2e4 9.5 / 8.7;
+//        R 80, S 4e5 28.8 / 25.3; FP32 R 8, S 1e6 43.6 / 43.9
+//   P 5: R 8, S 0 8.3 / 9.0; R 80, S 0 8.9 / 9.3; R 400, S 0 12.7 / 12.3;
+//        R 1, S 5000 9.0 / 8.6; R 1, S 2e4 9.5 / 8.7; R 8, S 4e5 26.8 / 25.2
+//   P 6: R 80, S 0 9.0 / 10.0; R 260, S 0 11.6 / 12.1; R 400, S 0 14.8 / 14.5;
+//        R 8, S 2500 9.0 / 9.4; R 8, S 5000 9.9 / 9.6; R 8, S 4e5 27.2 / 25.8;
+//        R 1, S 1.4e6 84.0 / 83.2; FP32 R 8, S 1e6 44.5 / 45.3
+//   P 7: R 8, S 1.4e6 86.3 / 88.0; R 80, S 2e5 22.4 / 20.1, 1.4e6 100.1 / 92.1
+//   P 8: R 40, S 0 8.0 / 10.6; R 8, S 2e4 9.4 / 10.8; R 80, S 2e4 11.2 / 11.5;
+//        R 8, S 1.4e6 85.4 / 90.6; R 80, S 4e5 29.2 / 28.5, 1.4e6 100.3 / 94.3
+constexpr int kMergeAlways = 4, kMergeBeside = 6, kMergeMany = 8;
+constexpr int64_t kMergeWhole = 384, kMergeSegs = 64, kMergeFull = 1536;
 void merge_short_splits(std::vector<Tile> &tiles);
 
 // Lanes of the segment sums of every whole tile: width_log2 holds, beside the
@@ -85,6 +99,9 @@ void merge_short_splits(std::vector<Tile> &tiles);
 // (bits 12-15).
 void choose_sum_lanes(std::vector<Tile> &tiles, const int32_t *ptr);
 
+// Slices are S contiguous ranges of the gathered index that hold about
+// nnz / S nonzeros each; gptr[nidx + 1] is the gathered dimension's own
+// pointer array (its nonzero counts as prefix sums).
 void slice_bounds(const hvec<int32_t> &gptr, int32_t nidx, int32_t S,
                   std::vector<int32_t> &bounds);
 void slice_format(const hvec<int32_t> &ptr, const hvec<int32_t> &idx, const hvec<int32_t> &gptr,

@@ -22,11 +22,12 @@
 // neighbouring entries together; pos then gives every nonzero's position in
 // the tile's segment order, where its product is stored in LDS, so the
 // segment sums are unchanged.
-// A segment longer than a tile is split into pieces.  Up to kMergePieces of
-// them stay in one workgroup, one after another; otherwise each piece's
-// workgroup publishes its part and the pieces are added in piece order by the
-// sliced step's combine, or by a small follow-up kernel.  The summation order
-// is fixed by the tiling alone, so results are bitwise reproducible run to run.
+// A segment longer than a tile is split into pieces.  Few of them may stay in
+// one workgroup, one after another (merge_short_splits); otherwise each
+// piece's workgroup publishes its part and the pieces are added in piece order
+// by the sliced step's combine, or by a small follow-up kernel.  The summation
+// order is fixed by the tiling alone, so results are bitwise reproducible run
+// to run.
 //
 // The XCD-sliced form (the paper's 2-D partition, Sec. 3.1 / App. D, across
 // the 8 XCDs): the gathered dimension is cut into S slices, slice s runs on

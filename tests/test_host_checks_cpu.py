@@ -34,3 +34,7 @@ def test_walks_end_at_the_largest_positions(tmp_path):
 def test_tile_kernel_holds_every_tile_size(tmp_path, nnz_max, segs_max):
     run_check(tmp_path, "tile_limits_check", f"-DDPDLP_TILE_NNZ_MAX={nnz_max}",
               f"-DDPDLP_TILE_SEGS_MAX={segs_max}")
+
+
+def test_merged_splits_keep_their_order_and_fill_the_chip(tmp_path):
+    run_check(tmp_path, "merge_check")
