@@ -136,6 +136,24 @@ constexpr int tile_loads(int tile_nnz)
     return per <= 1 ? 1 : per <= 2 ? 2 : per <= 4 ? 4 : per <= 8 ? 8 : kTileLoadsMax;
 }
 
+// LDS that the kernels of the largest tiles take without using it, so that
+// fewer of their workgroups share a CU: where many do, their gathers displace
+// each other's lines.  Not for the two-sided check pass on the tiles.  Us per
+// launch, with / without it (40M and 10M nonzeros with skewed columns, 9.4M
+// uniform, a LASSO of 6.9M, transportation LPs of 18M):
+//   FP64, one right-hand side (5 workgroups per CU / 7): dual step 40M 283 /
+//     290, 10M 69 / 74, uniform 68 / 69, transportation 73 / 76; primal step of
+//     the LASSO 46 / 48; check of the columns 50 / 53
+//   FP64 partial sums of two right-hand sides (3 / 4): 10M 100 / 113, 40M 631 /
+//     620, uniform 118 / 116, transportation 97 / 96
+//   FP32 (7 / 8): 10M dual 47.6 / 48.2, the others within 0.5%
+//   two-sided check pass on the tiles (3 / 4): LASSO 68.6 / 66.3, of 9.9M 108 /
+//     104, uniform 3.1M 49.0 / 48.4
+constexpr unsigned tile_pad(int tile_nnz, bool two_sided_check)
+{
+    return tile_nnz > 4 * kBlock && !two_sided_check ? 8192 : 0;
+}
+
 void set_error(const std::string &msg);
 
 // The nonzeros begin + first, begin + first + s, ... < end of a segment, s per

@@ -516,11 +516,7 @@ static void launch_tiles(dpdlp_problem *P, const Op &op, const TileSet &ts, cons
     const int remap = P->prm.xcd_remap ? 1 : 0;
     const int per_xcd = remap ? (ts.n + 7) / 8 : 0;
     const int grid = ts.blk2tile ? ts.grid : (remap ? 8 * per_xcd : ts.n);
-    // 8 KB of unused LDS keep the largest tiles at 5 workgroups per CU: with 6
-    // or 7 their gathers displace each other's lines (64 iterations of a
-    // 10M-nonzero skewed LP 10.86 ms, at 5 10.41; of a 40M-nonzero one 39.0,
-    // at 6 38.5, at 5 38.7)
-    const unsigned lds = P->prm.tile_nnz > 4 * kBlock ? 8192 : 0;
+    const unsigned lds = tile_pad(P->prm.tile_nnz, Op::NR == 2 && Op::NQ > 0);
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), lds, P->s, ts.d, ts.blk2tile, ts.n,
                            per_xcd, idx, val, seg_ptr, ts.seg_stride, (const uint16_t *)ts.pos,

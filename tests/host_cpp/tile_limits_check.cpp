@@ -1,6 +1,7 @@
 // Host check of the tile kernel's instantiation choice: for every tile size up
 // to the largest this build allows, the threads of a workgroup must be able to
-// load and stage a whole tile, and the tiles must respect the build's limits.
+// load and stage a whole tile, and the tiles must respect the build's limits;
+// and of the workgroups per CU that their LDS allows.
 // Built by tests/test_host_checks_cpu.py with the default limits and with
 // other ones (DPDLP_TILE_NNZ_MAX, DPDLP_TILE_SEGS_MAX).
 #include "dpdlp_internal.h"
@@ -18,6 +19,18 @@ int main()
         const int per = tile_loads(t);
         bad += per * kBlock < t;                        // a tile that does not fit
         bad += per > 1 && per <= 8 && per / 2 * kBlock >= t;    // a smaller one would do
+    }
+    // workgroups per CU of the largest tiles that 160 KB of LDS allow (products,
+    // segment pointers, at most 320 bytes of reductions, the pad)
+    if (kTileNnzMax == 2048 && kMaxSegs == 1024) {
+        auto wgs = [](int value_bytes, int sides, int sums, bool check) {
+            const int fixed = sides * 2048 * value_bytes + 1025 * 4 + sums * 32 + sides * 4 * value_bytes;
+            return 160 * 1024 / (fixed + (int)tile_pad(2048, check));
+        };
+        bad += wgs(8, 1, 1, false) != 5 || wgs(8, 1, 5, false) != 5;    // steps, column check
+        bad += wgs(8, 2, 1, false) != 3 || wgs(8, 2, 5, true) != 4;     // partials, row check
+        bad += wgs(4, 1, 1, false) != 7;
+        bad += tile_pad(1024, false) != 0 || tile_pad(1024, true) != 0;
     }
     // tiles, summing lanes and merged splits at the largest tile size
     std::mt19937 rng(3);
