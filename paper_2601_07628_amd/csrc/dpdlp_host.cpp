@@ -279,8 +279,13 @@ void choose_sum_lanes(std::vector<Tile> &tiles, const int32_t *ptr)
     }
     // several rounds of workgroups hide the latency that 2^h reads at once
     // save, and their unused reads cost LDS bandwidth: from 6M nonzeros on
-    // FP64 takes the other order always (64 iterations on 40M: 38.5 ms
-    // against 38.9; on 10M 10.30 against 10.35)
+    // FP64 takes the other order always.  64 iterations, always / only where
+    // it saves 5%, means of two runs that differ by up to 0.4%, ms: uniform
+    // 3.1M 2.82 / 2.81, 4.4M 3.84 / 3.86, 5.9M 4.98 / 4.96, 6.7M 5.86 / 5.91,
+    // 8.4M 7.83 / 7.83, 10.5M 10.11 / 10.14, 42M 40.17 / 40.17; skewed columns
+    // 3.2M 2.96 / 2.97, 4.5M 3.98 / 4.00, 6.0M 5.02 / 5.06, 6.8M 5.93 / 5.96,
+    // 8.5M 7.85 / 7.92, 10.6M 10.06 / 10.10, 16M 13.89 / 13.91, 42M 37.84 /
+    // 38.02; transportation 8M 6.17 / 6.16, LASSO 11M 10.15 / 10.15
     const bool large = nnz >= 6000000;
     const int nth = (int)std::min<int64_t>(host_threads(), 1 + segs / 16384);
     auto work = [&](int t) {
