@@ -352,6 +352,13 @@ void choose_sum_lanes(std::vector<Tile> &tiles, const int32_t *ptr)
     else run_threads(nth, work);
 }
 
+void plan_tiles(const int32_t *ptr, int32_t nseg, int32_t tile_nnz, std::vector<Tile> &tiles)
+{
+    build_tiles(ptr, nseg, tile_nnz, tiles);
+    merge_short_splits(tiles);
+    choose_sum_lanes(tiles, ptr);
+}
+
 void slice_bounds(const hvec<int32_t> &gptr, int32_t nidx, int32_t S,
                   std::vector<int32_t> &bounds)
 {

@@ -99,6 +99,10 @@ void merge_short_splits(std::vector<Tile> &tiles);
 // (bits 12-15).
 void choose_sum_lanes(std::vector<Tile> &tiles, const int32_t *ptr);
 
+// Tiles of one unsliced format, as the device gets them: build_tiles,
+// merge_short_splits, choose_sum_lanes.
+void plan_tiles(const int32_t *ptr, int32_t nseg, int32_t tile_nnz, std::vector<Tile> &tiles);
+
 // Slices are S contiguous ranges of the gathered index that hold about
 // nnz / S nonzeros each; gptr[nidx + 1] is the gathered dimension's own
 // pointer array (its nonzero counts as prefix sums).

@@ -19,6 +19,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <future>
 #include <memory>
 #include <string>
 #include <vector>
@@ -803,11 +804,9 @@ static int upload(dpdlp_problem *P, void *dst, const void *src, size_t bytes)
     return DPDLP_OK;
 }
 
-static int build_tileset(dpdlp_problem *P, const hvec<int32_t> &ptr, int32_t nseg,
-                         TileSet &ts, std::vector<Tile> &host_tiles)
+// Device copy of a format's tiles (plan_tiles).
+static int upload_tiles(dpdlp_problem *P, TileSet &ts, const std::vector<Tile> &host_tiles)
 {
-    build_tiles(ptr.data(), nseg, P->prm.tile_nnz, host_tiles);
-    merge_short_splits(host_tiles);
     ts.n = (int)host_tiles.size();
     std::vector<SplitSeg> sp;
     for (int i = 0; i < ts.n; ++i) {
@@ -815,14 +814,13 @@ static int build_tileset(dpdlp_problem *P, const hvec<int32_t> &ptr, int32_t nse
         if (t.npieces > 0 && t.piece == 0) sp.push_back(SplitSeg{t.seg_begin, i, t.npieces, t.slice});
     }
     ts.nsplit = (int)sp.size();
-    choose_sum_lanes(host_tiles, ptr.data());
     CHK(dalloc(P, &ts.d, host_tiles.size()));
     CHK(upload(P, ts.d, host_tiles.data(), host_tiles.size() * sizeof(Tile)));
     if (ts.nsplit) {
         CHK(dalloc(P, &ts.splits, sp.size()));
         CHK(upload(P, ts.splits, sp.data(), sp.size() * sizeof(SplitSeg)));
     }
-    HIPCHK(hipStreamSynchronize(P->s));     // host vectors are reused by the caller
+    HIPCHK(hipStreamSynchronize(P->s));     // sp goes out of scope
     return DPDLP_OK;
 }
 
@@ -1140,6 +1138,18 @@ static int create_impl(const dpdlp_csr_lp *lp_in, const dpdlp_params *params, vo
     P->h_perm_row = H.perm_row;
     P->h_perm_col = H.perm_col;
 
+    // A2: nonzero-aware workgroup tiles for both formats, planned while the
+    // matrix is uploaded (1M nonzeros: 0.9 ms of host work beside 24 MB, a
+    // creation 7.9 -> 7.6 ms; below 100k it takes less than starting a thread)
+    std::vector<Tile> tiles_r, tiles_c;
+    auto plan = [&]() {
+        plan_tiles(H.rp.data(), m, P->prm.tile_nnz, tiles_r);
+        plan_tiles(H.cp.data(), n, P->prm.tile_nnz, tiles_c);
+    };
+    std::future<void> planned;          // (waits where an upload fails first)
+    if (nnz >= 100000) planned = std::async(std::launch::async, plan);
+    else plan();
+
     CHK(dalloc(P, &P->rp, (size_t)m + 1)); CHK(dalloc(P, &P->ci, nnz)); CHK(dalloc(P, &P->v, nnz));
     CHK(dalloc(P, &P->cp, (size_t)n + 1)); CHK(dalloc(P, &P->ri, nnz)); CHK(dalloc(P, &P->vt, nnz));
     CHK(upload(P, P->rp, H.rp.data(), sizeof(int32_t) * ((size_t)m + 1)));
@@ -1150,10 +1160,9 @@ static int create_impl(const dpdlp_csr_lp *lp_in, const dpdlp_params *params, vo
         CHK(upload(P, P->ri, H.ri.data(), sizeof(int32_t) * nnz));
         CHK(upload(P, P->vt, H.vt.data(), sizeof(double) * nnz));
     }
-    // A2: nonzero-aware workgroup tiles for both formats
-    std::vector<Tile> ht;
-    CHK(build_tileset(P, H.rp, m, P->tr, ht));
-    CHK(build_tileset(P, H.cp, n, P->tc, ht));
+    if (planned.valid()) planned.get();
+    CHK(upload_tiles(P, P->tr, tiles_r));
+    CHK(upload_tiles(P, P->tc, tiles_c));
     int ntmax = std::max(P->tr.n, P->tc.n);
     // XCD-sliced fused steps: S > 0 slices both steps; S < 0 (automatic)
     // slices a step when its gathered vector exceeds one XCD's L2 (4 MB),
