@@ -926,12 +926,16 @@ inline unsigned nb(long n, int b = 256) { return (unsigned)((n + b - 1) / b); }
 // where there are fewer than 64 nodes for each
 unsigned dense_grid(int N) { return std::min(512u, nb(N, 64)); }
 
-// out = relu(IN W).  Below 16384 nodes one wave per 16 nodes and 32 features
-// (a launch is then one round trip, and filling 64 KB of LDS with W would be
-// the longest part of it), beyond it the persistent form.
+// out = relu(IN W).  Below kFewNodes one wave per 16 nodes and 32 features (a
+// launch is then one round trip, and filling 64 KB of LDS with W would be the
+// longest part of it), beyond it the persistent form.  A prediction with six
+// layer updates of N nodes each, few / persistent, us: N 1024 86 / 100, 4096
+// 85 / 112, 8192 99 / 115, 12288 117 / 119, 16384 137 / 124, 20480 159 / 140,
+// 32768 222 / 165, 65536 392 / 249.
+constexpr int kFewNodes = 12288;
 void dense(dpdlp_gnn *G, int N, const bf16 *IN, long off, bf16 *out, long ld)
 {
-    if (N < 16384)
+    if (N < kFewNodes)
         hipLaunchKernelGGL(k_dense_few, dim3(nb(N, 16)), dim3(256), 0, G->s, N, IN, G->wf + off, out, ld);
     else
         hipLaunchKernelGGL(k_dense, dim3(dense_grid(N)), dim3(256), 0, G->s, N, IN, G->wf + off, out, ld);
