@@ -130,9 +130,13 @@ typedef struct dpdlp_params {
                               /* 2 MB each (in the iterate's precision) and  */
                               /* each gathered element is read >= 4 times    */
                               /* per pass, else 8                            */
-    int32_t use_graphs;       /* 1: replay the check_period - 1 iterations    */
-                              /* between two checks as one HIP graph (off    */
-                              /* while dpdlp_profile_enable is on)           */
+    int32_t use_graphs;       /* 1: replay the last check_period - 2         */
+                              /* iterations before a check as one HIP graph, */
+                              /* where check_period > 2 and none of them is  */
+                              /* the call's last; a handle launches its      */
+                              /* first two such runs in a precision singly   */
+                              /* and captures the third (off while           */
+                              /* dpdlp_profile_enable is on)                 */
     int32_t perm_order;       /* 0: the block-wise random permutation alone; */
                               /* bit 0 (rows) / bit 1 (columns): hot-first, */
                               /* that order stably sorted by decreasing     */

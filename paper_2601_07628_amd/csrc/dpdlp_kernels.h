@@ -189,7 +189,8 @@ __device__ __forceinline__ void nt_store(T *p, T v)
 // a small tile issues no repeated loads and takes little LDS.  With PER = 8
 // for every tile size, shuffles through LDS in the segment sums and an LDS
 // buffer of their results, an iteration of a 10k-nonzero LP took 10.3 us
-// (now 8.2), of a 1M-nonzero LP 34.8 us (28.6; update and output included).
+// (8.2 without), of a 1M-nonzero LP 34.8 us (28.6; update and output
+// included); with the steps since then 6.9 and 23.5.
 constexpr int kPre = 2;                         // prefetched segments per thread
 
 template <class Op, int PER, bool NT>
